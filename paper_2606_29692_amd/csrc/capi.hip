@@ -117,6 +117,10 @@ extern "C" int vqe_destroy(vqe_ctx *ctx)
         (void)hipFree(ctx->ws);
     if (ctx->host_scalars)
         (void)hipHostFree(ctx->host_scalars);
+    if (ctx->stage)
+        (void)hipHostFree(ctx->stage);
+    if (ctx->stage_ev)
+        (void)hipEventDestroy(ctx->stage_ev);
     delete ctx;
     return VQE_OK;
 }

@@ -25,10 +25,17 @@ struct vqe_ctx {
     size_t ws_bytes;
     // Small pinned host buffer for scalar read-backs of the build phase.
     int64_t *host_scalars;
+    // Pinned staging of the operator builder's uploads (at most
+    // VQE_STAGE_BYTES, kept until the context goes) and the event of the last
+    // copy out of it.
+    void *stage;
+    hipEvent_t stage_ev;
     // This device's copy of the library's static scratch array (the
     // allocation-free entry points), or null if its address is unknown.
     double *scratch;
 };
+
+#define VQE_STAGE_BYTES ((size_t)1 << 20)
 
 // Record an error message on the context and return `status`.
 static inline int vqe_fail(vqe_ctx *ctx, int status, const char *fmt, ...)

@@ -1,0 +1,80 @@
+"""The CSR builder's kernels at the edges of their ranges: rows fewer than a
+wave, one and many waves per 64 rows, groups beyond the 64-row kernels' table,
+registers beyond its dense prefix table, operators passed as a kernel argument,
+through pinned staging and from pageable memory; every entry bit for bit the
+oracle's ordered sum."""
+import numpy as np
+import pytest
+
+from oracle import oracle as orc
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+import paper_2606_29692_amd as P  # noqa: E402
+from paper_2606_29692_amd import binding as B  # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    c = P.Context(0)
+    yield c
+    torch.cuda.synchronize()
+    c.close()
+
+
+def _terms(n, T, masks, real, seed):
+    """T terms over `masks` distinct flip masks, in random order, some cancelling."""
+    rng = np.random.default_rng(seed)
+    pick = rng.choice(1 << n, size=min(masks, 1 << n), replace=False).astype(np.uint64)
+    x = rng.choice(pick, size=T)
+    z = rng.integers(0, 1 << n, T).astype(np.uint64)
+    c = np.round(rng.standard_normal(T), 1) + 0j
+    if real:
+        c = np.where(np.bitwise_count(x & z) % 2 == 1, 1j * c, c)
+    else:
+        c = c + 1j * rng.standard_normal(T)
+    half = T // 4
+    return (np.concatenate([x, x[:half]]), np.concatenate([z, z[:half]]),
+            np.concatenate([c, -c[:half]]))
+
+
+@pytest.mark.parametrize("real", [False, True])
+@pytest.mark.parametrize("n,T,masks", [
+    (1, 3, 2), (3, 9, 8), (5, 40, 32), (6, 50, 20), (7, 7, 7), (7, 70, 63), (8, 90, 64),
+    (9, 400, 65), (10, 1500, 300), (11, 3000, 2048), (12, 1, 3000), (12, 60000, 1500),
+    (16, 60, 12), (21, 6, 3)])
+def test_csr_build_ranges(ctx, n, T, masks, real):
+    print(f"csr build n={n} T={T} masks={masks} real={real}", flush=True)
+    x, z, c = _terms(n, T, masks, real, 7 * n + T)
+    if masks > 2048:      # more groups than the supported row length: each vanishes on half its rows
+        x = np.repeat(np.random.default_rng(n).permutation(1 << n)[:masks].astype(np.uint64), 2)
+        z = np.where(np.arange(x.size) % 2 == 0, np.uint64(0), (x & np.uint64(1023)) + np.uint64(1))
+        c = np.where(np.bitwise_count(x & z) % 2 == 1, 1j, 1.0 + 0j) * (1.0 if real else 1j)
+    o = orc.csr_build(n, x, z, c)
+    d = B.csr_build_from_pauli(ctx, n, x, z, c)
+    torch.cuda.synchronize()
+    assert d.real == real and d.nnz == o.nnz
+    np.testing.assert_array_equal(d.rowptr.cpu().numpy().astype(np.int64), o.rowptr)
+    np.testing.assert_array_equal(d.col.cpu().numpy()[:o.nnz], o.col)
+    np.testing.assert_array_equal(d.val.cpu().numpy()[:o.nnz].view(np.uint64), o.val.view(np.uint64))
+
+
+@pytest.mark.parametrize("n,identity", [(2, False), (7, True), (10, False), (15, False)])
+def test_csr_build_shift_keeps_the_diagonal(ctx, n, identity):
+    """FP32 storage about a shift: every row stores its diagonal, present or not in the sum."""
+    x, z, c = _terms(n, 30, 5, True, n)
+    at = x != 0
+    x, z, c = x[at], z[at], c[at]
+    if identity:
+        x, z, c = np.append(x, np.uint64(0)), np.append(z, np.uint64(5)), np.append(c, 0.75)
+    d = B.csr_build_from_pauli(ctx, n, x, z, c, dtype="c64", diag_shift=0.5)
+    o = orc.csr_build(n, np.append(x, np.uint64(0)), np.append(z, np.uint64(0)), np.append(c, 1e3))
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(d.rowptr.cpu().numpy().astype(np.int64), o.rowptr)
+    np.testing.assert_array_equal(d.col.cpu().numpy(), o.col)
+    want = o.val.copy()
+    diag = o.col == np.repeat(np.arange(1 << n), np.diff(o.rowptr))
+    sign = 1.0 - 2.0 * (np.bitwise_count(o.col[diag].astype(np.uint64) & np.uint64(5)) % 2)
+    want[diag] = (0.75 * sign if identity else 0.0) - 0.5
+    np.testing.assert_array_equal(d.val.cpu().numpy(), want.astype(np.complex64))
