@@ -149,7 +149,13 @@ def plan_blocked(sched: int, d) -> bool:
         not real_tiled
 
 
-def stored_h_bytes(sched: int, ds, entries=None) -> int:
+def plan_dict(sched: int, d) -> bool:
+    """True when a state's sliced layout keeps most values in a dictionary."""
+    from paper_2606_29692_amd import binding as B
+    return bool(sched & B.VQE_SPMV_VDICT) and d.H.dim * d.psi.element_size() <= LDS_STATE_BYTES
+
+
+def stored_h_bytes(sched: int, ds, entries=None, layout_bytes=None) -> int:
     """Bytes the H-product kernel has to read and write per launch in the
     form it reads: row pointers, 2- or 4-byte columns, complex or real
     values (row-padded or not), the state and the result.  A blocked state
@@ -159,12 +165,19 @@ def stored_h_bytes(sched: int, ds, entries=None) -> int:
     columns and complex values, 2 bytes of row order per row (per row and
     column tile when tiled) and 8 bytes per slice (and per slab); with the
     flip-mask indices, 4 bytes per three entries and at most 2 KiB of masks
-    per row block in place of the columns."""
+    per row block in place of the columns.  With the value dictionary, the
+    layout's device bytes (``layout_bytes``) without what only its build uses,
+    and 10 KiB of tables per row block."""
     from paper_2606_29692_amd import binding as B
     x16, rv = plan_sched_x16(sched, ds), plan_sched_real(sched, ds)
     pad = rv or plan_sched_pad(sched, ds)
     tot = 0
     for i, d in enumerate(ds):
+        if plan_dict(sched, d):
+            build = 4 * (5 * 1024 + d.H.dim) + 2 * d.H.dim
+            tot += layout_bytes[i] - build + 10240 * -(-d.H.dim // BLK_ROWS) + \
+                2 * d.H.dim * d.psi.element_size()
+            continue
         if plan_sliced(sched, d):
             big = d.H.dim * d.psi.element_size() > LDS_STATE_BYTES
             nb = -(-d.H.dim // (SELLT_ROWS if big else BLK_ROWS))
@@ -655,6 +668,13 @@ def main():
         ts = form == "complex" and args.matrix_free
         leg = timed_leg(plan, stream, len(ds), thetas, K, W, L, R, tiled_screen=ts)
         leg["layout_entries"] = [plan.layout_entries(i) for i in range(len(ds))]
+        leg["layout_bytes"] = None
+        if plan_dict(sched, ds[0]):
+            leg["layout_bytes"] = []
+            for d in ds:
+                lay = B.Layout(ctx, d.H, sched)
+                leg["layout_bytes"].append(lay.nbytes())
+                lay.close()
         ph = eager_phases(plan, tiled_screen=ts)
         leg["tiled_screen"] = ts
         return sched, leg, ph, plan
@@ -662,12 +682,16 @@ def main():
     def form_record(form: str, sched: int, leg: dict, ph: dict) -> dict:
         acc = "complex" if form == "complex" else "real"
         nb = PB.bytes_per_step(ds, value_form=acc)
-        stored = stored_h_bytes(sched, ds, leg.pop("layout_entries"))
+        stored = stored_h_bytes(sched, ds, leg.pop("layout_entries"), leg.pop("layout_bytes"))
+        dic = plan_dict(sched, ds[0])
         h_s = leg["h_product_ms"] / 1e3
         achieved = nb["h_spmv"] / h_s / 1e9
         x16, rv = plan_sched_x16(sched, ds), plan_sched_real(sched, ds)
         return {
-            "schedule": sched, "value_form": "real parts" if rv else "complex",
+            "schedule": sched,
+            "value_form": "dictionary of real magnitudes, other entries " +
+                          ("their real parts" if ds[0].H.real else "complex") if dic else
+                          "real parts" if rv else "complex",
             "state_form": form, "algorithmic_bytes_per_step": nb,
             "byte_accounting": ("canonical CSR: int32 column + complex value per entry, each "
                                 "vector once" if acc == "complex" else
@@ -675,12 +699,15 @@ def main():
                                 "for a real H: the specialisation's own accounting, not the "
                                 "contract's") +
                                ("; the kernel reads the smaller stored form (stored_bytes_per_"
-                                "launch), so this fraction can approach 1 while the stored "
-                                "bytes stream below the peak (stored_GBps)"),
+                                "launch), so this fraction can approach 1 (with the value "
+                                "dictionary pass it: most values are not streamed) while the "
+                                "stored bytes stream below the peak (stored_GBps)"),
             "h_product_GBps": achieved, "h_product_frac_of_peak": achieved / HBM_PEAK_GBS,
             "traffic_bytes_per_launch": measured_traffic(sched, wl),
             "stored_bytes_per_launch": stored, "stored_GBps": stored / h_s / 1e9,
-            "column_form": (("10-bit flip-mask indices (three per 32-bit word)"
+            "column_form": (("12-bit codes of (flip mask, magnitude) pairs and the sign, and for "
+                             "the other entries " if dic else "") +
+                            ("10-bit flip-mask indices (three per 32-bit word)"
                              if sched & B.VQE_SPMV_XIDX and not plan_tiled(ds) else "16-bit columns") +
                             ", one row per lane in slices of 64 rows sorted by "
                             "length" + (" per column tile" if plan_tiled(ds) else "") +

@@ -654,6 +654,20 @@ VQE_API int64_t vqe_batch_workspace_bytes(const vqe_batch *plan);
  */
 #define VQE_SPMV_XIDX 0x80000
 /*
+ * With VQE_SPMV_XIDX, FP32 storage: a dictionary of the operator's values.  A
+ * flip mask whose entries take at most four magnitudes, all real (every
+ * two-electron mask of a molecular Hamiltonian), has them stored as 12-bit
+ * codes, the number of a (mask, magnitude) pair and a sign, beside a
+ * per-operator table of at most 1023 pairs (masks past that, and all others,
+ * keep the index form, as real parts for an operator flagged VQE_REAL).  The
+ * values are the CSR's, bit for bit.  Rows are
+ * sorted by their codes, then by their other entries; each lane adds its row's
+ * codes in ascending pair order, then the others in column order, so results
+ * agree with the other schedules to the rounding of FP64 sums.  Dropped where
+ * the index form is and in FP64 storage.
+ */
+#define VQE_SPMV_VDICT 0x100000
+/*
  * Time the H product (sigma = S psi with the energy reduction) with the given
  * schedule: `reps` back-to-back launches bracketed by HIP events on the
  * context stream; *ms_out = average milliseconds per launch.

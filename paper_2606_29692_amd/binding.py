@@ -33,6 +33,7 @@ VQE_SPMV_REAL = 0x8000
 VQE_SPMV_PAD = 0x10000
 VQE_SPMV_SLICED = 0x40000
 VQE_SPMV_XIDX = 0x80000
+VQE_SPMV_VDICT = 0x100000
 REL_TIE = 1e-6
 
 DTYPES = {"c128": VQE_C128, "c64": VQE_C64}

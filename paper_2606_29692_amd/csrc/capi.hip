@@ -385,49 +385,62 @@ int sliced_build(vqe_ctx *ctx, const vqe_csr *H, int sched, const SellBufs &b, S
                  int64_t *entries, int s)
 {
     const int E = sched & 0xff;
-    const bool xi = (sched & VQE_SPMV_XIDX) != 0;
+    const bool xi = (sched & VQE_SPMV_XIDX) != 0, vd = (sched & VQE_SPMV_VDICT) != 0;
     const int64_t nb = (H->dim + SPMV_LDS_ROWS - 1) / SPMV_LDS_ROWS;
-    const int64_t ns = nb * SPMV_SLICES_PER_BLOCK;
+    const int64_t ns = nb * SPMV_SLICES_PER_BLOCK, streams = vd ? 2 : 1;
     const size_t o_len = vqe_align((size_t)H->dim * sizeof(uint16_t));
-    const size_t o_sl = o_len + vqe_align((size_t)ns * sizeof(int32_t));
-    const size_t o_tot = o_sl + vqe_align((size_t)ns * sizeof(int2));
-    // the index form: the masks' marks, numbers, table and count
-    const size_t o_mark = o_tot + vqe_align(sizeof(int64_t));
-    const size_t o_xmap = o_mark + vqe_align((size_t)H->dim * sizeof(uint32_t));
+    const size_t o_sl = o_len + vqe_align((size_t)(streams * ns) * sizeof(int32_t));
+    const size_t o_tot = o_sl + vqe_align((size_t)(streams * ns) * sizeof(int2));
+    // the index form: the masks' count (after the totals), marks, numbers and table
+    const size_t o_mark = o_tot + vqe_align(3 * sizeof(int64_t));
+    const size_t o_xmap = o_mark + vqe_align((size_t)((H->dim + 31) / 32) * sizeof(uint32_t));
     const size_t o_xtab = o_xmap + vqe_align((size_t)H->dim * sizeof(uint16_t));
-    const size_t o_nx = o_xtab + vqe_align((size_t)SPMV_XIDX_MAX * sizeof(uint16_t));
-    const size_t need = xi ? o_nx + sizeof(int64_t) : o_tot + sizeof(int64_t);
+    // the dictionary: pairs, the masks' first pairs, scratch
+    const size_t o_pair = o_xtab + vqe_align((size_t)SPMV_XIDX_MAX * sizeof(uint16_t));
+    const size_t o_base = o_pair + vqe_align((size_t)SPMV_VD_PAIRS * sizeof(uint2));
+    const size_t o_vds = o_base + vqe_align((size_t)SPMV_XIDX_MAX * sizeof(uint16_t));
+    const size_t need = vd   ? o_vds + (size_t)launch_vd_scratch(H->dim) * sizeof(uint32_t)
+                        : xi ? o_pair
+                             : o_mark;
     int rc = grow_ctx(ctx, b.meta, b.meta_cap, (int64_t)need, "slice table", s);
     if (rc)
         return rc;
     char *m = (char *)*b.meta;
-    launch_sell_layout(H, E, (uint16_t *)m, (int32_t *)(m + o_len), (int2 *)(m + o_sl),
-                       (int64_t *)(m + o_tot), ctx->stream);
-    VQE_LAUNCH_CHECK(ctx);
-    if (xi) {
-        launch_sell_xtab(H, (uint32_t *)(m + o_mark), (uint16_t *)(m + o_xmap), (uint16_t *)(m + o_xtab),
-                         (int64_t *)(m + o_nx), ctx->stream);
-        VQE_LAUNCH_CHECK(ctx);
-    }
-    int64_t total = 0, nx = 0;
-    VQE_HIP(ctx, hipMemcpyAsync(&total, m + o_tot, sizeof(total), hipMemcpyDeviceToHost, ctx->stream));
+    int64_t *tot = (int64_t *)(m + o_tot);
     if (xi)
-        VQE_HIP(ctx, hipMemcpyAsync(&nx, m + o_nx, sizeof(nx), hipMemcpyDeviceToHost, ctx->stream));
+        launch_sell_xtab(H, (uint32_t *)(m + o_mark), (uint16_t *)(m + o_xmap), (uint16_t *)(m + o_xtab),
+                         tot + 2, ctx->stream);
+    if (vd)
+        launch_vd_layout(H, E, (const uint16_t *)(m + o_xmap), (const uint16_t *)(m + o_xtab), tot + 2,
+                         (uint32_t *)(m + o_vds), (uint2 *)(m + o_pair), (uint16_t *)(m + o_base), (uint16_t *)m,
+                         (int32_t *)(m + o_len), (int2 *)(m + o_sl), tot, ctx->stream);
+    else
+        launch_sell_layout(H, E, (uint16_t *)m, (int32_t *)(m + o_len), (int2 *)(m + o_sl), tot, ctx->stream);
+    VQE_LAUNCH_CHECK(ctx);
+    int64_t *h = ctx->host_scalars;     // the totals and the masks' count
+    VQE_HIP(ctx, hipMemcpyAsync(h, tot, 3 * sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
     VQE_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    if (total < 0 || total > 0x7fffffffLL)
-        return vqe_fail(ctx, VQE_ESIZE, "sliced layout of slot %d: %lld entries", s, (long long)total);
+    const int64_t total = h[0], codes = vd ? h[1] : 0, nx = xi ? h[2] : 0;
+    if (total < 0 || total > 0x7fffffffLL || codes < 0 || codes > 0x7fffffffLL)
+        return vqe_fail(ctx, VQE_ESIZE, "sliced layout of slot %d: %lld entries", s, (long long)(total + codes));
     if (nx < 0 || nx > SPMV_XIDX_MAX)
         return vqe_fail(ctx, VQE_ENOTSUP, "sliced layout of slot %d: %lld flip masks, more than the "
                         "index form's %d", s, (long long)nx, SPMV_XIDX_MAX);
     const int64_t n = total > 0 ? total : 1;
-    const bool real = (sched & VQE_SPMV_REAL) != 0;
+    const bool real = (sched & (VQE_SPMV_REAL | VQE_SPMV_RVALS)) != 0;
     const int64_t vb = (int64_t)vqe_elem_bytes(H->dtype) / (real ? 2 : 1);
-    // 16-bit columns, or one 32-bit word per three entries (whole groups)
-    const int64_t cb = xi ? (n + 2) / 3 * 4 + 8 : n * 2;
-    if ((rc = grow_ctx(ctx, b.code, b.code_cap, cb, "slice codes", s)) ||
+    // 16-bit columns, or one 32-bit word per three entries (whole groups),
+    // then the dictionary's codes
+    const int64_t cb = xi ? (int64_t)vqe_align((size_t)((n + 2) / 3 * 4 + 8)) : n * 2;
+    if ((rc = grow_ctx(ctx, b.code, b.code_cap, cb + (vd ? codes / SPMV_VD_GROUP * 16 + 16 : 0), "slice codes", s)) ||
         (rc = grow_ctx(ctx, b.val, b.val_cap, n * vb, "slice values", s)))
         return rc;
-    if (xi)
+    uint32_t *dcode = (uint32_t *)((char *)*b.code + cb);
+    if (vd)
+        launch_vd_fill(H, E, real, (const uint16_t *)m, (const int2 *)(m + o_sl), (const uint16_t *)(m + o_xmap),
+                       (const uint16_t *)(m + o_base), (const uint2 *)(m + o_pair), (uint32_t *)*b.code, *b.val,
+                       dcode, ctx->stream);
+    else if (xi)
         launch_sell_fill_x(H, E, real, (const uint16_t *)m, (const int2 *)(m + o_sl),
                            (const uint16_t *)(m + o_xmap), (uint32_t *)*b.code, *b.val, ctx->stream);
     else
@@ -440,7 +453,10 @@ int sliced_build(vqe_ctx *ctx, const vqe_csr *H, int sched, const SellBufs &b, S
     st.sslice = (const int2 *)(m + o_sl);
     st.sxtab = xi ? (const uint16_t *)(m + o_xtab) : nullptr;
     st.nx = (int32_t)nx;
-    *entries = total;
+    st.dcode = vd ? dcode : nullptr;
+    st.dslice = vd ? (const int2 *)(m + o_sl) + ns : nullptr;
+    st.dpair = vd ? (const uint2 *)(m + o_pair) : nullptr;
+    *entries = total + codes;
     return VQE_OK;
 }
 
@@ -828,6 +844,22 @@ extern "C" int vqe_batch_create(vqe_ctx *ctx, int32_t B, const vqe_batch_item *i
 
     // --- H product tasks, one table per lanes value
     std::map<int, std::vector<std::vector<int2>>> per_lanes, per_sum;
+    // dictionary schedules: a workgroup takes a whole block of rows, half or a
+    // quarter, whatever still gives at most one per CU: a block's state fills
+    // the LDS, so a CU holds one workgroup and idle CUs are the loss (complex states,
+    // whole blocks against these: 16 of 14 qubits 39 -> 28 us, 48 of 12 qubits
+    // 24 -> 18 us, one of 12 qubits 22 -> 10 us)
+    std::map<int, int> parts;
+    for (int s = 0; s < B; s++)
+        if (lanes[s] & VQE_SPMV_VDICT)
+            parts[lanes[s]] += (int)((items[s].H->dim + SPMV_LDS_ROWS - 1) / SPMV_LDS_ROWS);
+    for (auto &kv : parts) {
+        const int whole = SPMV_LDS_ROWS / SPMV_VD_PART_ROWS;
+        int np = whole;
+        while (np > 1 && kv.second * (whole / np) * 2 <= ctx->n_cu)
+            np /= 2;
+        kv.second = np;
+    }
     std::vector<int2> bounds_list;
     std::vector<std::pair<unsigned, unsigned>> bounds_range(B, {0u, 0u});
     for (int s = 0; s < B; s++) {
@@ -858,6 +890,13 @@ extern "C" int vqe_batch_create(vqe_ctx *ctx, int32_t B, const vqe_batch_item *i
             continue;
         }
         const int nb = (int)spmv_blocks(dim, lanes[s]);
+        if (lanes[s] & VQE_SPMV_VDICT) {
+            // (first part << 3) | parts, each task within a block of rows
+            const int np = parts[lanes[s]];
+            for (int b = 0; b < nb; b += np)
+                per[xcd_of[s]].push_back(make_int2(s, b << 3 | np));
+            continue;
+        }
         for (int b = 0; b < nb; b++)
             per[xcd_of[s]].push_back(make_int2(s, b));
     }
@@ -1385,6 +1424,9 @@ int rebind_impl(vqe_batch *p, int32_t slot, const vqe_batch_item *it, const vqe_
         st->sslice = layout->st.sslice;
         st->sxtab = layout->st.sxtab;
         st->nx = layout->st.nx;
+        st->dcode = layout->st.dcode;
+        st->dslice = layout->st.dslice;
+        st->dpair = layout->st.dpair;
         if (sched & VQE_SPMV_BLOCKED) {
             st->boff = layout->st.boff;
             st->smask = layout->st.smask;

@@ -316,7 +316,7 @@ void launch_sell_layout(const vqe_csr *H, int E, uint16_t *srow, int32_t *slen, 
 void launch_sell_fill(const vqe_csr *H, int E, bool real, const uint16_t *srow,
                       const int2 *sslice, uint16_t *code, void *val, hipStream_t s);
 // flip-mask index form (VQE_SPMV_XIDX): the masks col ^ row the operator
-// uses, numbered ascending (xmap [dim], with mark [dim] as scratch), the
+// uses, numbered ascending (xmap [dim], with mark [dim / 32] as scratch), the
 // first SPMV_XIDX_MAX of them in xtab and their count in *nx ...
 void launch_sell_xtab(const vqe_csr *H, uint32_t *mark, uint16_t *xmap, uint16_t *xtab, int64_t *nx,
                       hipStream_t s);
@@ -324,6 +324,19 @@ void launch_sell_xtab(const vqe_csr *H, uint32_t *mark, uint16_t *xmap, uint16_t
 // 32-bit word per three entries) and the values
 void launch_sell_fill_x(const vqe_csr *H, int E, bool real, const uint16_t *srow, const int2 *sslice,
                         const uint16_t *xmap, uint32_t *code, void *val, hipStream_t s);
+// value dictionary (VQE_SPMV_VDICT, FP32 storage, after launch_sell_xtab): the
+// pairs pair [SPMV_VD_PAIRS] and each mask's first one base [SPMV_XIDX_MAX],
+// the row order, and for the entries beside the dictionary, then for the
+// codes, the slices' lengths slen, the slices sslice [2 * slices] and the
+// totals total [2]; scratch: launch_vd_scratch words ...
+inline int64_t launch_vd_scratch(int64_t dim) { return SPMV_XIDX_MAX * (SPMV_VD_VALS + 1) + dim; }
+void launch_vd_layout(const vqe_csr *H, int E, const uint16_t *xmap, const uint16_t *xtab,
+                      const int64_t *nx, uint32_t *scratch, uint2 *pair, uint16_t *base,
+                      uint16_t *srow, int32_t *slen, int2 *sslice, int64_t *total, hipStream_t s);
+// ... then, with room for the totals, both streams
+void launch_vd_fill(const vqe_csr *H, int E, bool real, const uint16_t *srow, const int2 *sslice,
+                    const uint16_t *xmap, const uint16_t *base, const uint2 *pair, uint32_t *code,
+                    void *val, uint32_t *dcode, hipStream_t s);
 // sliced layout of a column-tiled state (VQE_SPMV_SLICED on a state larger
 // than LDS): per slab of the blocked layout (nt tiles of tc columns) the row
 // order srow [slabs * SPMV_SELLT_ROWS] (first the rows' entry counts), the

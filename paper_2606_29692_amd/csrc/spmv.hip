@@ -950,20 +950,31 @@ k_sell_sort(const int32_t *__restrict__ rowptr, int64_t dim, int E, uint16_t *__
     }
 }
 
-// Slice starts (entries) in slice order and the total; one thread (a state
-// that fits LDS has at most a few hundred slices).
-__global__ void k_sell_scan(const int32_t *__restrict__ slen, int64_t ns, int2 *__restrict__ sslice,
-                            int64_t *__restrict__ total)
+// Slice starts (entries) in slice order and the total; one wave per stream of
+// slices (the entries, and with VQE_SPMV_VDICT the dictionary codes).
+__global__ void __launch_bounds__(64)
+k_sell_scan(const int32_t *__restrict__ slen, int64_t ns, int2 *__restrict__ sslice,
+            int64_t *__restrict__ total)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0)
-        return;
-    int64_t at = 0;
-    for (int64_t c = 0; c < ns; c++) {
-        const int len = slen[c];
-        sslice[c] = make_int2((int)at, len);
-        at += (int64_t)len * VQE_WAVE;
+    const int lane = threadIdx.x;
+    slen += (int64_t)blockIdx.x * ns;
+    sslice += (int64_t)blockIdx.x * ns;
+    int64_t carry = 0;
+    for (int64_t c0 = 0; c0 < ns; c0 += VQE_WAVE) {
+        const int len = c0 + lane < ns ? slen[c0 + lane] : 0;
+        int64_t inc = len;
+#pragma unroll
+        for (int o = 1; o < VQE_WAVE; o <<= 1) {
+            const int64_t t = __shfl_up(inc, o, VQE_WAVE);
+            if (lane >= o)
+                inc += t;
+        }
+        if (c0 + lane < ns)
+            sslice[c0 + lane] = make_int2((int)((carry + inc - len) * VQE_WAVE), len);
+        carry += __shfl(inc, VQE_WAVE - 1, VQE_WAVE);
     }
-    *total = at;
+    if (lane == 0)
+        total[blockIdx.x] = carry * VQE_WAVE;
 }
 
 // Codes and values of one slice per wave (pads: column dim, value zero); RV:
@@ -1005,40 +1016,53 @@ k_sell_fill(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
 // uses (Eq. 3: every Pauli string maps r to r ^ x), numbered in ascending
 // order, and the slices' entries stored as those numbers.
 __global__ void __launch_bounds__(256)
-k_sell_xclear(uint32_t *__restrict__ mark, int64_t dim)
+k_sell_fill32(uint32_t *__restrict__ p, int64_t n, uint32_t v)
 {
-    const int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (x < dim)
-        mark[x] = 0u;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n)
+        p[i] = v;
 }
 
-// mark[x] = 1 for every mask the operator uses; one thread per row (col and
-// row are below dim = 2^N, so is their XOR).
+// Rows of a workgroup of the kernels that read the whole CSR (a wave per row).
+#define SELL_SCAN_ROWS 64
+
+// The masks the operator uses, a bit each in mark [dim / 32 words, at least
+// one] (col and row are below dim = 2^N <= 2^16, so is their XOR); a
+// workgroup's rows gather in LDS first.
 __global__ void __launch_bounds__(256)
 k_sell_xmark(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col, int64_t dim,
              uint32_t *__restrict__ mark)
 {
-    const int64_t r = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (r >= dim)
-        return;
-    for (int k = rowptr[r]; k < rowptr[r + 1]; k++)
-        mark[(uint32_t)col[k] ^ (uint32_t)r] = 1u;
+    __shared__ uint32_t s_mark[SPMV_X16_MAX_DIM / 32];
+    const int tid = threadIdx.x, lane = tid & 63, words = (int)((dim + 31) / 32);
+    for (int i = tid; i < words; i += 256)
+        s_mark[i] = 0u;
+    __syncthreads();
+    const int64_t r0 = (int64_t)blockIdx.x * SELL_SCAN_ROWS;
+    for (int64_t r = r0 + (tid >> 6); r < r0 + SELL_SCAN_ROWS && r < dim; r += 4)
+        for (int k = rowptr[r] + lane; k < rowptr[r + 1]; k += VQE_WAVE) {
+            const uint32_t x = (uint32_t)col[k] ^ (uint32_t)r;
+            if (!(s_mark[x >> 5] >> (x & 31u) & 1u))
+                atomicOr(&s_mark[x >> 5], 1u << (x & 31u));
+        }
+    __syncthreads();
+    for (int i = tid; i < words; i += 256)
+        if (s_mark[i])
+            atomicOr(&mark[i], s_mark[i]);
 }
 
 // The masks' numbers xmap[x] (ascending x), the table xtab[number] = x for
-// the first SPMV_XIDX_MAX numbers and the count; one workgroup (dim <= 2^16).
+// the first SPMV_XIDX_MAX numbers and the count; one workgroup (dim <= 2^16:
+// at most two words of mark per thread).
 __global__ void __launch_bounds__(1024)
 k_sell_xscan(const uint32_t *__restrict__ mark, int64_t dim, uint16_t *__restrict__ xmap,
              uint16_t *__restrict__ xtab, int64_t *__restrict__ nx)
 {
     __shared__ int part[1024];
-    const int tid = threadIdx.x;
-    const int64_t per = (dim + 1023) / 1024;
-    const int64_t lo = (int64_t)tid * per < dim ? (int64_t)tid * per : dim;
-    const int64_t hi = lo + per < dim ? lo + per : dim;
-    int c = 0;
-    for (int64_t x = lo; x < hi; x++)
-        c += mark[x] != 0u;
+    const int tid = threadIdx.x, words = (int)((dim + 31) / 32);
+    const uint32_t w0 = 2 * tid < words ? mark[2 * tid] : 0u;
+    const uint32_t w1 = 2 * tid + 1 < words ? mark[2 * tid + 1] : 0u;
+    const int c = __popc(w0) + __popc(w1);
     part[tid] = c;
     __syncthreads();
     for (int off = 1; off < 1024; off <<= 1) {
@@ -1048,8 +1072,10 @@ k_sell_xscan(const uint32_t *__restrict__ mark, int64_t dim, uint16_t *__restric
         __syncthreads();
     }
     int at = part[tid] - c;
-    for (int64_t x = lo; x < hi; x++)
-        if (mark[x]) {
+#pragma unroll
+    for (int h = 0; h < 2; h++)
+        for (uint32_t w = h ? w1 : w0; w; w &= w - 1) {
+            const uint32_t x = (uint32_t)(2 * tid + h) * 32u + (uint32_t)__builtin_ctz(w);
             xmap[x] = (uint16_t)at;
             if (at < SPMV_XIDX_MAX)
                 xtab[at] = (uint16_t)x;
@@ -1057,6 +1083,315 @@ k_sell_xscan(const uint32_t *__restrict__ mark, int64_t dim, uint16_t *__restric
         }
     if (tid == 1023)
         *nx = part[1023];
+}
+
+// ---- value dictionary (VQE_SPMV_VDICT): a flip mask whose entries take at
+// most SPMV_VD_VALS magnitudes, all real (in a molecular Hamiltonian every
+// two-electron mask: its entries are +- one integral, or one of three sums),
+// has its entries stored as a code, the number of the (mask, magnitude) pair
+// and the sign, beside a per-operator table of the pairs.  At 14 qubits 511 of
+// 554 masks and 136.5 of 158.5 entries per row, in 651 pairs.
+//
+// What it is for: the sliced product streamed 9.3 bytes per entry at the rate
+// HBM gives (64 states of 14 qubits: 1.6 GB, 275 us).  Twelve-bit codes for
+// those entries and real parts for the others of a real H leave 0.4 GB; the
+// product is then bound by the vector ALU (about ten operations an entry) and
+// the LDS gathers about as much as by HBM: 96 us.  Sixteen-bit codes with the
+// sign beside them took 113 us, twelve bits with an unsigned table 109 us.
+#define SPMV_VD_EMPTY 0xffffffffu
+
+// Collect each mask's magnitudes (bits of |re|): slots [SPMV_XIDX_MAX *
+// SPMV_VD_VALS], all SPMV_VD_EMPTY before, and bad [SPMV_XIDX_MAX], zero
+// before, set for a mask with more or with an imaginary part.  The set found
+// does not depend on the order of the insertions.
+__device__ __forceinline__ void vd_insert(uint32_t *slots, uint32_t *bad, int i, uint32_t v)
+{
+    for (int q = 0; q < SPMV_VD_VALS; q++) {
+        uint32_t cur = __hip_atomic_load(&slots[i * SPMV_VD_VALS + q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (cur == SPMV_VD_EMPTY)
+            cur = atomicCAS(&slots[i * SPMV_VD_VALS + q], SPMV_VD_EMPTY, v);
+        if (cur == SPMV_VD_EMPTY || cur == v)
+            return;
+    }
+    bad[i] = 1u;
+}
+
+__global__ void __launch_bounds__(256)
+k_vd_collect(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
+             const float2 *__restrict__ val, int64_t dim, const uint16_t *__restrict__ xmap,
+             uint32_t *__restrict__ slots, uint32_t *__restrict__ bad)
+{
+    __shared__ uint32_t s_slots[SPMV_XIDX_MAX * SPMV_VD_VALS];
+    __shared__ uint32_t s_bad[SPMV_XIDX_MAX];
+    const int tid = threadIdx.x, lane = tid & 63;
+    for (int i = tid; i < SPMV_XIDX_MAX * SPMV_VD_VALS; i += 256)
+        s_slots[i] = SPMV_VD_EMPTY;
+    for (int i = tid; i < SPMV_XIDX_MAX; i += 256)
+        s_bad[i] = 0u;
+    __syncthreads();
+    const int64_t r0 = (int64_t)blockIdx.x * SELL_SCAN_ROWS;
+    for (int64_t r = r0 + (tid >> 6); r < r0 + SELL_SCAN_ROWS && r < dim; r += 4)
+        for (int k = rowptr[r] + lane; k < rowptr[r + 1]; k += VQE_WAVE) {
+            const int i = xmap[(uint32_t)col[k] ^ (uint32_t)r];
+            const float2 v = val[k];
+            if (i >= SPMV_XIDX_MAX || s_bad[i])     // (too many masks: refused later)
+                continue;
+            if (v.y != 0.f)
+                s_bad[i] = 1u;
+            else
+                vd_insert(s_slots, s_bad, i, __float_as_uint(v.x) & 0x7fffffffu);
+        }
+    __syncthreads();
+    for (int i = tid; i < SPMV_XIDX_MAX; i += 256) {
+        if (s_bad[i]) {
+            bad[i] = 1u;
+            continue;
+        }
+        for (int q = 0; q < SPMV_VD_VALS; q++)
+            if (s_slots[i * SPMV_VD_VALS + q] != SPMV_VD_EMPTY)
+                vd_insert(slots, bad, i, s_slots[i * SPMV_VD_VALS + q]);
+    }
+}
+
+// Number the pairs, masks ascending and each one's magnitudes ascending:
+// pair [SPMV_VD_PAIRS] = (magnitude, byte offset of the mask in a staged
+// state), zero past the last (the pads' pair SPMV_VD_PAIRS - 1 among them),
+// and base [SPMV_XIDX_MAX] the first pair of each mask, or SPMV_VD_NONE for a
+// mask that keeps its entries as they are.
+#define SPMV_VD_NONE 0xffffu
+__global__ void __launch_bounds__(1024)
+k_vd_number(const uint32_t *__restrict__ slots, const uint32_t *__restrict__ bad,
+            const uint16_t *__restrict__ xtab, const int64_t *__restrict__ nx,
+            uint2 *__restrict__ pair, uint16_t *__restrict__ base)
+{
+    static_assert(SPMV_XIDX_MAX == 1024 && SPMV_VD_PAIRS == 1024 && SPMV_VD_VALS == 4, "one thread each");
+    __shared__ int part[1024];
+    const int tid = threadIdx.x;
+    uint32_t v[4] = {SPMV_VD_EMPTY, SPMV_VD_EMPTY, SPMV_VD_EMPTY, SPMV_VD_EMPTY};
+    int c = 0;
+    if (tid < *nx && !bad[tid]) {
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+            v[q] = slots[tid * 4 + q];
+        // ascending (the empty ones last)
+#pragma unroll
+        for (int a = 0; a < 3; a++)
+#pragma unroll
+            for (int q = 0; q < 3 - a; q++)
+                if (v[q] > v[q + 1]) {
+                    const uint32_t t = v[q];
+                    v[q] = v[q + 1];
+                    v[q + 1] = t;
+                }
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+            c += v[q] != SPMV_VD_EMPTY;
+    }
+    part[tid] = c;
+    pair[tid] = make_uint2(0u, 0u);
+    __syncthreads();
+    for (int off = 1; off < 1024; off <<= 1) {
+        const int t = tid >= off ? part[tid - off] : 0;
+        __syncthreads();
+        part[tid] += t;
+        __syncthreads();
+    }
+    const int at = part[tid] - c;
+    const bool in = c > 0 && at + c <= SPMV_VD_PAIRS - 1;
+    base[tid] = in ? (uint16_t)at : (uint16_t)SPMV_VD_NONE;
+    if (in)
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+            if (q < c)
+                pair[at + q] = make_uint2(v[q], (uint32_t)xtab[tid] * (uint32_t)sizeof(float2));
+}
+
+// Entries of each row in the dictionary (low half) and beside it (high half).
+__global__ void __launch_bounds__(256)
+k_vd_rows(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col, int64_t dim,
+          const uint16_t *__restrict__ xmap, const uint16_t *__restrict__ base,
+          uint32_t *__restrict__ len)
+{
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int64_t r0 = (int64_t)blockIdx.x * SELL_SCAN_ROWS;
+    for (int64_t r = r0 + (tid >> 6); r < r0 + SELL_SCAN_ROWS && r < dim; r += 4) {
+        const int k0 = rowptr[r], k1 = rowptr[r + 1];
+        int n = 0;
+        for (int k = k0; k < k1; k += VQE_WAVE) {
+            bool d = false;
+            if (k + lane < k1) {
+                const int i = xmap[(uint32_t)col[k + lane] ^ (uint32_t)r];
+                d = i < SPMV_XIDX_MAX && base[i] != SPMV_VD_NONE;
+            }
+            n += __popcll(__ballot(d));
+        }
+        if (lane == 0)
+            len[r] = (uint32_t)n | (uint32_t)(k1 - k0 - n) << 16;
+    }
+}
+
+// k_sell_sort for the two streams: rows by dictionary entries, then by the
+// others (longest first, ties by row); slice lengths of the others, rounded up
+// to E, then [at slen + slices] of the codes, rounded up to SPMV_VD_GROUP.
+__global__ void __launch_bounds__(1024)
+k_vd_sort(const uint32_t *__restrict__ len, int64_t dim, int E, uint16_t *__restrict__ srow,
+          int32_t *__restrict__ slen, int64_t ns)
+{
+    __shared__ uint64_t key[SPMV_LDS_ROWS];
+    const int tid = threadIdx.x;
+    const int64_t r0 = (int64_t)blockIdx.x * SPMV_LDS_ROWS;
+    const int n = (int)(dim - r0 < SPMV_LDS_ROWS ? dim - r0 : SPMV_LDS_ROWS);
+    for (int i = tid; i < SPMV_LDS_ROWS; i += 1024) {
+        uint64_t k = ~0ull;   // no row: sorts last
+        if (i < n) {
+            const uint32_t l = len[r0 + i];
+            k = (uint64_t)(0xffffu - (l & 0xffffu)) << 32 | (uint64_t)(0xffffu - (l >> 16)) << 16 | (uint32_t)i;
+        }
+        key[i] = k;
+    }
+    __syncthreads();
+    for (int k = 2; k <= SPMV_LDS_ROWS; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            // the lower row of each compared pair, one pair per thread
+            const int i = ((tid & ~(j - 1)) << 1) | (tid & (j - 1)), q = i | j;
+            const uint64_t a = key[i], b = key[q];
+            if ((a > b) == ((i & k) == 0)) {
+                key[i] = b;
+                key[q] = a;
+            }
+            __syncthreads();
+        }
+    for (int i = tid; i < n; i += 1024)
+        srow[r0 + i] = (uint16_t)(key[i] & 0xffffu);
+    const int lane = tid & 63;
+    for (int c = tid >> 6; c < SPMV_SLICES_PER_BLOCK; c += 16) {
+        const int i = c * VQE_WAVE + lane;
+        int d = 0, e = 0;
+        if (i < n) {
+            d = (int)(0xffffu - (uint32_t)(key[i] >> 32));
+            e = (int)(0xffffu - (uint32_t)(key[i] >> 16 & 0xffffu));
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            d = max(d, __shfl_xor(d, o, VQE_WAVE));
+            e = max(e, __shfl_xor(e, o, VQE_WAVE));
+        }
+        if (lane == 0) {
+            const int64_t at = (int64_t)blockIdx.x * SPMV_SLICES_PER_BLOCK + c;
+            slen[at] = (e + E - 1) / E * E;
+            slen[ns + at] = (d + SPMV_VD_GROUP - 1) / SPMV_VD_GROUP * SPMV_VD_GROUP;
+        }
+    }
+}
+
+// A word of codes: one in bits 3 to 14 (in place for a byte offset into a
+// table of 8-byte elements), one in bits 15 to 26, eight bits of a third in
+// bits 27 to 31 and 0 to 2.
+__device__ __forceinline__ uint32_t vd_word(uint32_t a, uint32_t b, uint32_t e)
+{
+    return a << 3 | b << 15 | e << 27 | e >> 5;
+}
+__device__ __forceinline__ uint32_t vd_byte(uint32_t w) { return __builtin_amdgcn_alignbit(w, w, 27) & 0xffu; }
+
+// Both streams of one slice per workgroup, a row per wave in turn.  A row's
+// codes go in ascending pair order (neighbouring lanes then read neighbouring
+// pairs), its other entries in column order.
+template <bool RV, int E>
+__global__ void __launch_bounds__(1024)
+k_vd_fill(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
+          const float2 *__restrict__ val, int64_t dim, const uint16_t *__restrict__ srow,
+          const int2 *__restrict__ sslice, int64_t ns, const uint16_t *__restrict__ xmap,
+          const uint16_t *__restrict__ base, const uint2 *__restrict__ pair,
+          uint32_t *__restrict__ code, typename ValOf<VQE_C64, RV>::T *__restrict__ out,
+          uint32_t *__restrict__ dcode)
+{
+    using V = typename ValOf<VQE_C64, RV>::T;
+    // a row's codes, then its other entries' mask numbers (a row has one entry
+    // per mask, so both fit)
+    __shared__ uint32_t s_bits[16][SPMV_VD_PAIRS / 32];
+    __shared__ uint16_t s_pre[16][SPMV_VD_PAIRS / 32];
+    __shared__ uint16_t s_row[16][SPMV_XIDX_MAX];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    uint32_t *bits = s_bits[wid];
+    uint16_t *pre = s_pre[wid], *buf = s_row[wid];
+    const int64_t c = blockIdx.x;
+    const int64_t r0 = (c / SPMV_SLICES_PER_BLOCK) * SPMV_LDS_ROWS;
+    const int n = (int)(dim - r0 < SPMV_LDS_ROWS ? dim - r0 : SPMV_LDS_ROWS);
+    const int2 se = sslice[c], sd = sslice[ns + c];
+    for (int lr = wid; lr < VQE_WAVE; lr += 16) {
+        const int i = (int)(c % SPMV_SLICES_PER_BLOCK) * VQE_WAVE + lr;
+        int64_t row = 0;
+        int k0 = 0, k1 = 0;
+        if (i < n) {
+            row = r0 + srow[r0 + i];
+            k0 = rowptr[row];
+            k1 = rowptr[row + 1];
+        }
+        auto pair_of = [&](int k, int &m) -> int {     // the entry's pair, or -1; its mask's number
+            m = xmap[(uint32_t)col[k] ^ (uint32_t)row];
+            const uint32_t b = base[m];
+            if (b == SPMV_VD_NONE)
+                return -1;
+            const uint32_t v = __float_as_uint(val[k].x) & 0x7fffffffu;
+            int p = (int)b;
+            for (int q = 0; q < SPMV_VD_VALS - 1 && pair[p].x != v; q++)
+                p++;
+            return p;
+        };
+        if (lane < SPMV_VD_PAIRS / 32)
+            bits[lane] = 0u;
+        for (int k = k0 + lane; k < k1; k += VQE_WAVE) {
+            int m;
+            const int p = pair_of(k, m);
+            if (p >= 0)
+                atomicOr(&bits[p >> 5], 1u << (p & 31));
+        }
+        int inc = lane < SPMV_VD_PAIRS / 32 ? __popc(bits[lane]) : 0;
+        const int own = inc;
+#pragma unroll
+        for (int o = 1; o < VQE_WAVE; o <<= 1) {
+            const int t = __shfl_up(inc, o, VQE_WAVE);
+            if (lane >= o)
+                inc += t;
+        }
+        if (lane < SPMV_VD_PAIRS / 32)
+            pre[lane] = (uint16_t)(inc - own);
+        const int nd = __shfl(inc, VQE_WAVE - 1, VQE_WAVE);
+        auto eat = [&](int j) { return (int64_t)se.x + ((int64_t)(j / E) * VQE_WAVE + lr) * E + j % E; };
+        int ne = 0;
+        for (int kb = k0; kb < k1; kb += VQE_WAVE) {
+            const int k = kb + lane;
+            int m = 0, p = -1;
+            const bool on = k < k1;
+            if (on)
+                p = pair_of(k, m);
+            const uint64_t eb = __ballot(on && p < 0);
+            if (on && p >= 0) {
+                const int j = pre[p >> 5] + __popc(bits[p >> 5] & ((1u << (p & 31)) - 1u));
+                buf[j] = (uint16_t)((uint32_t)p << 1 | __float_as_uint(val[k].x) >> 31);
+            } else if (on) {
+                const int j = ne + __popcll(eb & ((1ull << lane) - 1ull));
+                buf[nd + j] = (uint16_t)m;
+                if constexpr (RV)
+                    out[eat(j)] = val[k].x;
+                else
+                    out[eat(j)] = val[k];
+            }
+            ne += __popcll(eb);
+        }
+        auto code_at = [&](int j) { return j < nd ? (uint32_t)buf[j] : 2u * (SPMV_VD_PAIRS - 1); };
+        for (int w = lane; w < sd.y / SPMV_VD_GROUP * 4; w += VQE_WAVE) {
+            const int g = w >> 2, q = w & 3, j = g * SPMV_VD_GROUP;
+            const uint32_t x = code_at(j + 8 + (q >> 1));
+            dcode[(int64_t)sd.x / SPMV_VD_GROUP * 4 + ((int64_t)g * VQE_WAVE + lr) * 4 + q] =
+                vd_word(code_at(j + 2 * q), code_at(j + 2 * q + 1), q & 1 ? x >> 8 : x & 0xffu);
+        }
+        for (int j = ne + lane; j < se.y; j += VQE_WAVE)
+            out[eat(j)] = V{};
+        auto idx_at = [&](int j) { return j < ne ? (uint32_t)buf[nd + j] : 0u; };
+        for (int w = lane; w < se.y / 3; w += VQE_WAVE)
+            code[eat(3 * w) / 3] = idx_at(3 * w) | idx_at(3 * w + 1) << 10 | idx_at(3 * w + 2) << 20;
+    }
 }
 
 // Indices and values of one slice per wave (E = 3 or 6 entries per group,
@@ -1280,8 +1615,8 @@ struct SellGroupX {
     }
 };
 
-// One wave's share of a block of the sliced layout: slices A = wid and
-// B = wid + 16 (those the block has), taken as one stream of groups (A's,
+// One wave's share of a block of the sliced layout: its slices A and B (those
+// the block has; a whole block: wid and wid + 16), taken as one stream of groups (A's,
 // then B's) so that B's first groups load while A finishes; D groups of E
 // entries per lane in flight.  Every load is issued (past the stream's end
 // it repeats the last group, which is in cache), so no load sits under a
@@ -1295,16 +1630,18 @@ struct SellWave {
     const V *val;
     int64_t r0, ata, atb;
     int n, ns, nga, ngb, ng, ra, rb;   // ra, rb: block-local rows of this lane
+    int ka, kb;                        // the slices (none: past the block's)
     G g[D];
 
-    __device__ __forceinline__ void init(const SpmvState &st, int blk, int lane, int wid)
+    __device__ __forceinline__ void init(const SpmvState &st, int blk, int lane, int a_slice, int b_slice)
     {
+        ka = a_slice;
+        kb = b_slice;
         code = reinterpret_cast<const typename G::C *>(st.scode);
         val = reinterpret_cast<const V *>(st.sval);
         r0 = (int64_t)blk * SPMV_LDS_ROWS;
         n = (int)(st.dim - r0 < SPMV_LDS_ROWS ? st.dim - r0 : SPMV_LDS_ROWS);
         ns = (n + VQE_WAVE - 1) / VQE_WAVE;
-        const int ka = wid, kb = wid + 16;
         const sell_v2i *sls = reinterpret_cast<const sell_v2i *>(st.sslice) + (int64_t)blk * SPMV_SLICES_PER_BLOCK;
         sell_v2i a = {0, 0}, b = {0, 0};
         if (ka < ns)
@@ -1383,6 +1720,113 @@ struct SellWave {
     }
 };
 
+// One wave's share of a block's dictionary codes: its slices A and B as one stream of groups of SPMV_VD_GROUP codes (16 bytes per
+// lane), D groups in flight, as SellWave.  An entry is one read of its signed
+// pair, one of the state at row ^ mask and two FMAs (one for a real state).
+template <int D> struct DictWave {
+    const sell_v4u *code;
+    int64_t ata, atb;
+    int nga, ngb, ng;
+    sell_v4u g[D];
+
+    __device__ __forceinline__ void init(const SpmvState &st, int blk, int lane, int ka, int kb, int ns)
+    {
+        code = reinterpret_cast<const sell_v4u *>(st.dcode);
+        const sell_v2i *sls = reinterpret_cast<const sell_v2i *>(st.dslice) + (int64_t)blk * SPMV_SLICES_PER_BLOCK;
+        sell_v2i a = {0, 0}, b = {0, 0};
+        if (ka < ns)
+            a = gmem(sls)[ka];
+        if (kb < ns)
+            b = gmem(sls)[kb];
+        nga = __builtin_amdgcn_readfirstlane(a.y) / SPMV_VD_GROUP;
+        ngb = __builtin_amdgcn_readfirstlane(b.y) / SPMV_VD_GROUP;
+        ng = nga + ngb;
+        ata = __builtin_amdgcn_readfirstlane(a.x) / SPMV_VD_GROUP + lane;
+        atb = __builtin_amdgcn_readfirstlane(b.x) / SPMV_VD_GROUP + lane - (int64_t)nga * VQE_WAVE;
+    }
+    __device__ __forceinline__ sell_v4u load(int p) const
+    {
+        const int pc = p < ng ? p : ng - 1;
+        return gmem(code)[(pc < nga ? ata : atb) + (int64_t)pc * VQE_WAVE];
+    }
+    __device__ __forceinline__ void prefetch()
+    {
+#pragma unroll
+        for (int d = 0; d < D; d++)
+            g[d] = load(d);
+    }
+    template <typename X>
+    static __device__ __forceinline__ void use(const sell_v4u c, const unsigned char *s_x,
+                                               const unsigned char *s_pair, uint32_t row8, double &are, double &aim)
+    {
+        // byte offsets of the ten signed pairs (vd_word)
+        uint32_t at[SPMV_VD_GROUP];
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            at[2 * q] = c[q] & 0x7ff8u;
+            at[2 * q + 1] = c[q] >> 12 & 0x7ff8u;
+        }
+#pragma unroll
+        for (int q = 0; q < 2; q++)
+            at[8 + q] = (vd_byte(c[2 * q]) | vd_byte(c[2 * q + 1]) << 8) << 3;
+        uint2 pr[SPMV_VD_GROUP];
+#pragma unroll
+        for (int q = 0; q < SPMV_VD_GROUP; q++)
+            pr[q] = *reinterpret_cast<const uint2 *>(s_pair + at[q]);
+        X x[SPMV_VD_GROUP];
+#pragma unroll
+        for (int q = 0; q < SPMV_VD_GROUP; q++)
+            x[q] = *reinterpret_cast<const X *>(s_x + (row8 ^ pr[q].y));
+#pragma unroll
+        for (int q = 0; q < SPMV_VD_GROUP; q++)
+            sell_fma(__uint_as_float(pr[q].x), x[q], are, aim);
+    }
+    // the sums of rows ra (A) and rb (B) over their codes; X: 8-byte elements
+    template <typename X>
+    __device__ __forceinline__ void run(const X *s_xe, const uint2 *s_pairs, int64_t ra, int64_t rb,
+                                        double2 &sa, double2 &sb)
+    {
+        static_assert(sizeof(X) == 8, "the pairs hold byte offsets of 8-byte elements");
+        const unsigned char *s_x = reinterpret_cast<const unsigned char *>(s_xe);
+        const unsigned char *s_pair = reinterpret_cast<const unsigned char *>(s_pairs);
+        double are = 0.0, aim = 0.0;
+        sa = make_double2(0.0, 0.0);
+        sb = make_double2(0.0, 0.0);
+        if (ng == 0)
+            return;
+        uint32_t row8 = (uint32_t)ra * 8u;
+        int q = 0;
+        for (; q + D <= ng; q += D) {
+#pragma unroll
+            for (int d = 0; d < D; d++) {
+                if (q + d == nga) {
+                    sa = make_double2(are, aim);
+                    are = aim = 0.0;
+                    row8 = (uint32_t)rb * 8u;
+                }
+                const sell_v4u c = g[d];
+                g[d] = load(q + D + d);
+                use<X>(c, s_x, s_pair, row8, are, aim);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+#pragma unroll
+        for (int d = 0; d < D; d++)
+            if (q + d < ng) {
+                if (q + d == nga) {
+                    sa = make_double2(are, aim);
+                    are = aim = 0.0;
+                    row8 = (uint32_t)rb * 8u;
+                }
+                use<X>(g[d], s_x, s_pair, row8, are, aim);
+            }
+        if (ngb == 0)
+            sa = make_double2(are, aim);
+        else
+            sb = make_double2(are, aim);
+    }
+};
+
 // The block's rows from a wave's sums: sigma (FP32 storage: gathered in LDS
 // and stored in row order), the energy terms and the block's partials.
 template <int DT, int E, int D, bool RV, bool XI, typename X>
@@ -1429,6 +1873,57 @@ __device__ __forceinline__ void sell_finish(const SpmvState &st, int blk, const 
     }
 }
 
+// The same for np parts (SPMV_VD_PART_ROWS sorted rows each) of a block from
+// part p0 on, with a triple of partials per part: the sums' order is the same
+// however the parts are split over workgroups.  A whole block's results leave
+// in row order; a split one's rows lie all over the block and leave one by one.
+template <int E, int D, bool RV, typename X>
+__device__ __forceinline__ void vd_finish(const SpmvState &st, int blk, int p0, int np,
+                                          const SellWave<VQE_C64, E, D, RV, true> &w, const X *s_x,
+                                          float2 *s_sig, double2 sa, double2 sb)
+{
+    constexpr int SLICES = SPMV_VD_PART_ROWS / VQE_WAVE, PARTS = SPMV_LDS_ROWS / SPMV_VD_PART_ROWS;
+    __shared__ double s_part[SPMV_SLICES_PER_BLOCK][3];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const bool whole = np == PARTS;
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+        const int k = h ? w.kb : w.ka;
+        if (k >= SPMV_SLICES_PER_BLOCK)
+            continue;
+        double e_re = 0.0, e_im = 0.0, e_n2 = 0.0;
+        const int i = k * VQE_WAVE + lane;
+        if (k < w.ns && i < w.n) {
+            const int64_t row = w.r0 + (h ? w.rb : w.ra);
+            const double2 a = h ? sb : sa;
+            if (whole)
+                s_sig[row - w.r0] = make_float2((float)a.x, (float)a.y);
+            else
+                Elem<VQE_C64>::st(st.sigma, row, a);
+            energy_terms(s_x[row], a.x, a.y, e_re, e_im, e_n2);
+        }
+        e_re = wave_sum(e_re);
+        e_im = wave_sum(e_im);
+        e_n2 = wave_sum(e_n2);
+        if (lane == 0) {
+            s_part[k][0] = e_re;
+            s_part[k][1] = e_im;
+            s_part[k][2] = e_n2;
+        }
+    }
+    __syncthreads();
+    if (whole)
+        for (int i = tid; i < w.n; i += 1024)
+            stg(reinterpret_cast<float2 *>(st.sigma), w.r0 + i, s_sig[i]);
+    const int p = p0 + tid / 3, q = tid % 3;
+    if (tid < 3 * np && p * SPMV_VD_PART_ROWS < w.n) {
+        double v = 0.0;
+        for (int k = 0; k < SLICES; k++)
+            v += s_part[p * SLICES + k][q];
+        gmem(st.partials)[((int64_t)blk * PARTS + p) * 3 + q] = v;
+    }
+}
+
 // One workgroup per (state, block of SPMV_LDS_ROWS rows): the state staged in
 // LDS (plus the zero element), then the block's slices; each wave's first
 // groups are loaded together with the staged state.  With RV (the real parts
@@ -1438,7 +1933,7 @@ __device__ __forceinline__ void sell_finish(const SpmvState &st, int blk, const 
 // masks staged after the block's results (every one of the SPMV_XIDX_MAX
 // slots written, zero past the operator's count, so every index gives a
 // column below dim).
-template <int DT, int E, int D, bool RV, bool XI>
+template <int DT, int E, int D, bool RV, bool XI, bool VD, bool RS>
 __global__ void __launch_bounds__(1024) VQE_LDS_OCCUPANCY
 k_spmv_sell(const SpmvState *__restrict__ states, const int2 *__restrict__ tasks)
 {
@@ -1457,23 +1952,76 @@ k_spmv_sell(const SpmvState *__restrict__ states, const int2 *__restrict__ tasks
     float2 *s_sig = reinterpret_cast<float2 *>(smem + (size_t)(dim + 1) * sizeof(T));
     uint16_t *s_xt = reinterpret_cast<uint16_t *>(
         smem + (size_t)(dim + 1) * sizeof(T) + (DT == VQE_C64 ? SPMV_LDS_ROWS * sizeof(float2) : 0));
+    // VD: the signed pairs where the results go later
+    static_assert(2 * SPMV_VD_PAIRS * sizeof(uint2) == SPMV_LDS_ROWS * sizeof(float2), "pairs in the results' place");
+    uint2 *s_pair = reinterpret_cast<uint2 *>(s_sig);
+    // a task is a block, or with VD np of its parts from p0 on: one slice per
+    // wave when they are fewer than all
+    int blk = t.y, p0 = 0, np = 0, ka = wid, kb = wid + 16;
+    if constexpr (VD) {
+        constexpr int PARTS = SPMV_LDS_ROWS / SPMV_VD_PART_ROWS, SLICES = SPMV_VD_PART_ROWS / VQE_WAVE;
+        np = t.y & 7;
+        p0 = (t.y >> 3) % PARTS;
+        blk = (t.y >> 3) / PARTS;
+        if (np != PARTS) {
+            ka = wid < np * SLICES ? p0 * SLICES + wid : SPMV_SLICES_PER_BLOCK;
+            kb = SPMV_SLICES_PER_BLOCK;
+        }
+    }
     SellWave<DT, E, D, RV, XI> w;
-    w.init(st, t.y, lane, wid);
+    w.init(st, blk, lane, ka, kb);
     if constexpr (XI) {
         static_assert(SPMV_XIDX_MAX <= 1024, "one mask per thread");
         s_xt[tid] = tid < st.nx ? gmem(st.sxtab)[tid] : (uint16_t)0;
     }
+    // VD: the dictionary's codes run first, then the other entries, whose first
+    // groups load meanwhile
+    static_assert(!VD || (XI && DT == VQE_C64), "the dictionary form: FP32 storage, with the index form");
+    DictWave<SPMV_VD_DEPTH> dw;
+    if constexpr (VD) {
+        const sell_v2u pr = gmem(reinterpret_cast<const sell_v2u *>(st.dpair))[tid];
+        s_pair[2 * tid] = make_uint2(pr.x, pr.y);
+        s_pair[2 * tid + 1] = make_uint2(pr.x ^ 0x80000000u, pr.y);
+        dw.init(st, blk, lane, ka, kb, w.ns);
+    }
     double2 sa, sb;
-    if constexpr (RV) {
-        if (w.ng > 0)
+    auto products = [&](const auto *s_x) {
+        if constexpr (VD) {
+            double2 da, db;
+            if (w.ng > 0)
+                w.prefetch();
+            dw.run(s_x, s_pair, w.r0 + w.ra, w.r0 + w.rb, da, db);
+            w.run(s_x, s_xt, sa, sb);
+            sa = make_double2(sa.x + da.x, sa.y + da.y);
+            sb = make_double2(sb.x + db.x, sb.y + db.y);
+            __syncthreads();      // the results take the pairs' place
+        } else {
+            w.run(s_x, s_xt, sa, sb);
+        }
+    };
+    auto finish = [&](const auto *s_x) {
+        if constexpr (VD)
+            vd_finish(st, blk, p0, np, w, s_x, s_sig, sa, sb);
+        else
+            sell_finish(st, blk, w, s_x, s_sig, sa, sb);
+    };
+    auto first_groups = [&]() {
+        if constexpr (VD) {
+            if (dw.ng > 0)
+                dw.prefetch();
+        } else if (w.ng > 0) {
             w.prefetch();
+        }
+    };
+    if constexpr (RS) {
+        first_groups();
         double *s_xr = reinterpret_cast<double *>(smem);
         const int cplx = stage_real<8>(s_xr, psi, dim, tid);
         if (tid == 0)
             s_xr[dim] = 0.0;
         if (!__syncthreads_or(cplx)) {
-            w.run(s_xr, s_xt, sa, sb);
-            sell_finish(st, t.y, w, s_xr, s_sig, sa, sb);
+            products(s_xr);
+            finish(s_xr);
             return;
         }
     }
@@ -1492,8 +2040,8 @@ k_spmv_sell(const SpmvState *__restrict__ states, const int2 *__restrict__ tasks
         if (c < nch)
             pre[u] = gmem(src)[c];
     }
-    if (!RV && w.ng > 0)
-        w.prefetch();
+    if (!RS)
+        first_groups();
 #pragma unroll
     for (int u = 0; u < SP; u++) {
         const int64_t c = tid + 1024 * u;
@@ -1505,8 +2053,8 @@ k_spmv_sell(const SpmvState *__restrict__ states, const int2 *__restrict__ tasks
     if (tid == 0)
         s_x[dim] = T{};
     __syncthreads();
-    w.run(s_x, s_xt, sa, sb);
-    sell_finish(st, t.y, w, s_x, s_sig, sa, sb);
+    products(s_x);
+    finish(s_x);
 }
 
 // Column-tiled variant of the pipelined LDS schedule, for states larger than
@@ -2183,16 +2731,20 @@ static void launch_spmv_pf_t(const SpmvState &single, const SpmvState *states, c
 
 // Sliced schedules: E entries per lane and load group, D groups in flight;
 // rv: the real parts of the values (VQE_SPMV_REAL).
-template <int DT, int E, int D, bool XI = false>
+template <int DT, int E, int D, bool XI = false, bool VD = false>
 static void launch_sell_t(const SpmvState *states, const int2 *tasks, unsigned grid, hipStream_t s,
-                          size_t lds, bool rv)
+                          size_t lds, int sched)
 {
     // the state (with its zero element; lds counts it with the row pointers
     // of the other LDS schedules), in FP32 storage a block of results, and
     // the flip masks of the index form
     lds = lds - (SPMV_LDS_ROWS + 1) * sizeof(int32_t) +
           (DT == VQE_C64 ? SPMV_LDS_ROWS * sizeof(float2) : 0) + (XI ? SPMV_XIDX_MAX * sizeof(uint16_t) : 0);
-    auto k = rv ? k_spmv_sell<DT, E, D, true, XI> : k_spmv_sell<DT, E, D, false, XI>;
+    const bool rs = (sched & VQE_SPMV_REAL) != 0;
+    auto k = rs ? k_spmv_sell<DT, E, D, true, XI, VD, true> : k_spmv_sell<DT, E, D, false, XI, VD, false>;
+    if constexpr (VD)
+        if (!rs && (sched & VQE_SPMV_RVALS))
+            k = k_spmv_sell<DT, E, D, true, XI, VD, false>;
     (void)hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     k<<<grid, 1024, lds, s>>>(states, tasks);
 }
@@ -2205,18 +2757,25 @@ static void launch_spmv_dt(int sched, const SpmvState &single, const SpmvState *
         // the sliced layout exists only in batch plans; E = 2, 4 or 8
         // (FP64 values keep half as many groups in flight: the registers)
         constexpr bool W = DT == VQE_C128;
-        const bool rv = (sched & VQE_SPMV_REAL) != 0;
+        if constexpr (DT == VQE_C64)
+            if (sched & VQE_SPMV_VDICT) {
+                if ((sched & 0xff) == 3)
+                    launch_sell_t<DT, 3, 4, true, true>(states, tasks, grid, s, lds, sched);
+                else
+                    launch_sell_t<DT, 6, 2, true, true>(states, tasks, grid, s, lds, sched);
+                return;
+            }
         if (sched & VQE_SPMV_XIDX) {
             if ((sched & 0xff) == 3)
-                launch_sell_t<DT, 3, W ? 2 : 6, true>(states, tasks, grid, s, lds, rv);
+                launch_sell_t<DT, 3, W ? 2 : 6, true>(states, tasks, grid, s, lds, sched);
             else
-                launch_sell_t<DT, 6, W ? 1 : 3, true>(states, tasks, grid, s, lds, rv);
+                launch_sell_t<DT, 6, W ? 1 : 3, true>(states, tasks, grid, s, lds, sched);
             return;
         }
         switch (sched & 0xff) {
-        case 2: launch_sell_t<DT, 2, W ? 2 : 4>(states, tasks, grid, s, lds, rv); return;
-        case 8: launch_sell_t<DT, 8, W ? 1 : 2>(states, tasks, grid, s, lds, rv); return;
-        default: launch_sell_t<DT, 4, W ? 2 : 3>(states, tasks, grid, s, lds, rv); return;
+        case 2: launch_sell_t<DT, 2, W ? 2 : 4>(states, tasks, grid, s, lds, sched); return;
+        case 8: launch_sell_t<DT, 8, W ? 1 : 2>(states, tasks, grid, s, lds, sched); return;
+        default: launch_sell_t<DT, 4, W ? 2 : 3>(states, tasks, grid, s, lds, sched); return;
         }
     }
     constexpr int D = VQE_SPMV_LDS | VQE_SPMV_DEEP;
@@ -2765,16 +3324,52 @@ void launch_sell_layout(const vqe_csr *H, int E, uint16_t *srow, int32_t *slen, 
 {
     const int64_t nb = (H->dim + SPMV_LDS_ROWS - 1) / SPMV_LDS_ROWS;
     k_sell_sort<<<(unsigned)nb, 1024, 0, s>>>(H->rowptr, H->dim, E, srow, slen);
-    k_sell_scan<<<1, 64, 0, s>>>(slen, nb * SPMV_SLICES_PER_BLOCK, sslice, total);
+    k_sell_scan<<<1, VQE_WAVE, 0, s>>>(slen, nb * SPMV_SLICES_PER_BLOCK, sslice, total);
+}
+
+static void fill32(uint32_t *p, int64_t n, uint32_t v, hipStream_t s)
+{
+    k_sell_fill32<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(p, n, v);
 }
 
 void launch_sell_xtab(const vqe_csr *H, uint32_t *mark, uint16_t *xmap, uint16_t *xtab, int64_t *nx,
                       hipStream_t s)
 {
-    const unsigned g = (unsigned)((H->dim + 255) / 256);
-    k_sell_xclear<<<g, 256, 0, s>>>(mark, H->dim);
+    const unsigned g = (unsigned)((H->dim + SELL_SCAN_ROWS - 1) / SELL_SCAN_ROWS);
+    fill32(mark, (H->dim + 31) / 32, 0u, s);
     k_sell_xmark<<<g, 256, 0, s>>>(H->rowptr, H->col, H->dim, mark);
     k_sell_xscan<<<1, 1024, 0, s>>>(mark, H->dim, xmap, xtab, nx);
+}
+
+void launch_vd_layout(const vqe_csr *H, int E, const uint16_t *xmap, const uint16_t *xtab,
+                      const int64_t *nx, uint32_t *scratch, uint2 *pair, uint16_t *base,
+                      uint16_t *srow, int32_t *slen, int2 *sslice, int64_t *total, hipStream_t s)
+{
+    const unsigned g = (unsigned)((H->dim + SELL_SCAN_ROWS - 1) / SELL_SCAN_ROWS);
+    const int64_t nb = (H->dim + SPMV_LDS_ROWS - 1) / SPMV_LDS_ROWS, ns = nb * SPMV_SLICES_PER_BLOCK;
+    uint32_t *slots = scratch, *bad = slots + SPMV_XIDX_MAX * SPMV_VD_VALS, *len = bad + SPMV_XIDX_MAX;
+    fill32(slots, SPMV_XIDX_MAX * SPMV_VD_VALS, SPMV_VD_EMPTY, s);
+    fill32(bad, SPMV_XIDX_MAX, 0u, s);
+    k_vd_collect<<<g, 256, 0, s>>>(H->rowptr, H->col, (const float2 *)H->val, H->dim, xmap, slots, bad);
+    k_vd_number<<<1, 1024, 0, s>>>(slots, bad, xtab, nx, pair, base);
+    k_vd_rows<<<g, 256, 0, s>>>(H->rowptr, H->col, H->dim, xmap, base, len);
+    k_vd_sort<<<(unsigned)nb, 1024, 0, s>>>(len, H->dim, E, srow, slen, ns);
+    k_sell_scan<<<2, VQE_WAVE, 0, s>>>(slen, ns, sslice, total);
+}
+
+void launch_vd_fill(const vqe_csr *H, int E, bool real, const uint16_t *srow, const int2 *sslice,
+                    const uint16_t *xmap, const uint16_t *base, const uint2 *pair, uint32_t *code,
+                    void *val, uint32_t *dcode, hipStream_t s)
+{
+    const int64_t nb = (H->dim + SPMV_LDS_ROWS - 1) / SPMV_LDS_ROWS, ns = nb * SPMV_SLICES_PER_BLOCK;
+    auto go = [&](auto k, auto *out) {
+        k<<<(unsigned)ns, 1024, 0, s>>>(H->rowptr, H->col, (const float2 *)H->val, H->dim, srow, sslice, ns,
+                                        xmap, base, pair, code, out, dcode);
+    };
+    if (real)
+        E == 3 ? go(k_vd_fill<true, 3>, (float *)val) : go(k_vd_fill<true, 6>, (float *)val);
+    else
+        E == 3 ? go(k_vd_fill<false, 3>, (float2 *)val) : go(k_vd_fill<false, 6>, (float2 *)val);
 }
 
 template <int E>
@@ -2949,6 +3544,10 @@ bool vqe_valid_schedule(int sched)
     case 3 | VQE_SPMV_LDS | VQE_SPMV_SLICED | VQE_SPMV_XIDX | VQE_SPMV_REAL:
     case 6 | VQE_SPMV_LDS | VQE_SPMV_SLICED | VQE_SPMV_XIDX:
     case 6 | VQE_SPMV_LDS | VQE_SPMV_SLICED | VQE_SPMV_XIDX | VQE_SPMV_REAL:
+    case 3 | VQE_SPMV_LDS | VQE_SPMV_SLICED | VQE_SPMV_XIDX | VQE_SPMV_VDICT:
+    case 3 | VQE_SPMV_LDS | VQE_SPMV_SLICED | VQE_SPMV_XIDX | VQE_SPMV_VDICT | VQE_SPMV_REAL:
+    case 6 | VQE_SPMV_LDS | VQE_SPMV_SLICED | VQE_SPMV_XIDX | VQE_SPMV_VDICT:
+    case 6 | VQE_SPMV_LDS | VQE_SPMV_SLICED | VQE_SPMV_XIDX | VQE_SPMV_VDICT | VQE_SPMV_REAL:
         return true;
     default:
         return false;
@@ -2970,8 +3569,16 @@ int vqe_effective_schedule(const vqe_csr *H, int sched)
             (H->dim + 1) * (int64_t)vqe_elem_bytes(H->dtype) + SPMV_LDS_ROWS * (int64_t)sizeof(float2) +
                     SPMV_XIDX_MAX * (int64_t)sizeof(uint16_t) > 160 * 1024)
             sched = (sched & ~(VQE_SPMV_XIDX | 0xff)) | 4;
+        // the dictionary comes with the index form, in FP32 storage; beside it
+        // the entries of an operator flagged real are stored as real parts
+        // whatever the state
+        sched &= ~VQE_SPMV_RVALS;
+        if (!(sched & VQE_SPMV_XIDX) || H->dtype != VQE_C64)
+            sched &= ~VQE_SPMV_VDICT;
+        else if ((sched & VQE_SPMV_VDICT) && (H->flags & VQE_REAL))
+            sched |= VQE_SPMV_RVALS;
         // the real values need an operator flagged real
-        return sched & (VQE_SPMV_SLICED | VQE_SPMV_LDS | VQE_SPMV_XIDX | 0xff |
+        return sched & (VQE_SPMV_SLICED | VQE_SPMV_LDS | VQE_SPMV_XIDX | VQE_SPMV_VDICT | VQE_SPMV_RVALS | 0xff |
                         ((H->flags & VQE_REAL) ? VQE_SPMV_REAL : 0));
     }
     // four lanes per row exist only in the blocked product of states larger
@@ -3014,7 +3621,7 @@ int vqe_batch_schedule(const vqe_csr *H, int sched)
     if ((sched & VQE_SPMV_SLICED) && big) {
         // (the index form's states fit LDS; larger ones take two entries per group)
         if (sched & VQE_SPMV_XIDX)
-            sched = (sched & ~(VQE_SPMV_XIDX | 0xff)) | 2;
+            sched = (sched & ~(VQE_SPMV_XIDX | VQE_SPMV_VDICT | 0xff)) | 2;
         return (sched & (0xff | VQE_SPMV_LDS | VQE_SPMV_SLICED | VQE_SPMV_DEEP)) | VQE_SPMV_TILED |
                VQE_SPMV_BLOCKED;
     }
@@ -3070,7 +3677,9 @@ void launch_col_xor16(const vqe_csr *H, uint16_t *col16, hipStream_t s)
 
 int64_t spmv_blocks(int64_t dim, int sched)
 {
-    const int64_t rpb = (sched & VQE_SPMV_LDS) ? SPMV_LDS_ROWS : spmv_rows_per_block(sched);
+    const int64_t rpb = (sched & VQE_SPMV_VDICT) ? SPMV_VD_PART_ROWS
+                        : (sched & VQE_SPMV_LDS) ? SPMV_LDS_ROWS
+                                                 : spmv_rows_per_block(sched);
     return (dim + rpb - 1) / rpb;
 }
 

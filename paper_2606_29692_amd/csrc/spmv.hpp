@@ -91,6 +91,18 @@ struct SpmvState {
     // holding entry j of lane i in bits 10 * (j % 3)
     const uint16_t *sxtab;
     int32_t nx;
+    // value dictionary (VQE_SPMV_VDICT): the pairs dpair[SPMV_VD_PAIRS]
+    // (magnitude, byte offset of the flip mask in a staged state) and per slice
+    // the codes of the rows' entries that the dictionary holds, dslice as
+    // sslice (starts and lengths in codes): lane i's j-th code is in the four
+    // 32-bit words at 4 * (start / SPMV_VD_GROUP + (j / SPMV_VD_GROUP) * 64 + i),
+    // codes 2q and 2q + 1 of the ten in word q, the ninth spread over words 0
+    // and 1, the tenth over 2 and 3 (vd_word); a code is twice the pair's
+    // number, plus one for a negative value (pads: the last pair, which is
+    // zero).  scode, sval and sslice then hold the other entries
+    const uint32_t *dcode;
+    const int2 *dslice;
+    const uint2 *dpair;
 };
 
 // Column-tiled H product: tile width (state elements staged in LDS per pass)
@@ -116,6 +128,19 @@ struct SpmvState {
 #define SPMV_SLICES_PER_BLOCK (SPMV_LDS_ROWS / VQE_WAVE)
 // flip-mask index form: table entries (10-bit indices)
 #define SPMV_XIDX_MAX 1024
+// value dictionary: pairs (the last one is the pads'), magnitudes per mask,
+// codes per lane and load (12 bits each in 16 bytes), loads in flight per lane
+#define SPMV_VD_PAIRS 1024
+// sorted rows of a block that one workgroup may take alone, with their own
+// partial sums (a quarter of a block)
+#define SPMV_VD_PART_ROWS 512
+// (internal schedule bit) the values beside a dictionary are real parts
+#define VQE_SPMV_RVALS 0x200000
+#define SPMV_VD_VALS 4
+#define SPMV_VD_GROUP 10
+#ifndef SPMV_VD_DEPTH
+#define SPMV_VD_DEPTH 3
+#endif
 // largest dimension whose column XOR row fits 16 bits
 #define SPMV_X16_MAX_DIM 65536
 // row length granule of the padded layout (real values, states that fit LDS)

@@ -6,8 +6,9 @@ the pipelined loads (PREFETCH), 16-bit column codes (X16), the complex
 values in the row-padded layout (PAD), for a real H the real values in
 that layout (REAL), and the sliced layout with one row per lane (SLICED,
 with 2, 4 or 8 entries per lane and load in place of the lanes, or 3 or 6
-with the flip masks' 10-bit indices in place of the columns, XIDX; an
-operator with too many masks for it times as infinite).  It is picked
+with the flip masks' 10-bit indices in place of the columns, XIDX, and a
+dictionary of the values, VDICT; an operator with too many masks for it times
+as infinite).  It is picked
 per (register size, dtype, mapping, value form, device) by timing the batched
 H product phase of a real plan over the candidates, and cached.  The value
 form "complex" keeps the interleaved complex values of the CSR (candidates
@@ -36,7 +37,7 @@ from . import binding as B
 
 _L, _V, _D, _P = B.VQE_SPMV_LDS, B.VQE_SPMV_VEC4, B.VQE_SPMV_DEEP, B.VQE_SPMV_PREFETCH
 _X, _R, _Q, _S = B.VQE_SPMV_X16, B.VQE_SPMV_REAL, B.VQE_SPMV_PAD, B.VQE_SPMV_SLICED
-_I = B.VQE_SPMV_XIDX
+_I, _K = B.VQE_SPMV_XIDX, B.VQE_SPMV_VDICT
 CANDIDATES = (8, 16, 32, 64, 16 | _V, 32 | _V, 64 | _V,
               8 | _L, 16 | _L, 32 | _L, 64 | _L, 8 | _L | _D, 16 | _L | _D, 32 | _L | _D, 64 | _L | _D,
               32 | _L | _P, 64 | _L | _P, 32 | _L | _P | _D, 64 | _L | _P | _D,
@@ -54,7 +55,10 @@ CANDIDATES = (8, 16, 32, 64, 16 | _V, 32 | _V, 64 | _V,
               2 | _L | _S, 4 | _L | _S, 8 | _L | _S, 2 | _L | _S | _D, 4 | _L | _S | _D,
               2 | _L | _S | _R, 4 | _L | _S | _R, 8 | _L | _S | _R,
               # and with the flip masks' 10-bit indices in place of the columns
-              3 | _L | _S | _I, 6 | _L | _S | _I, 3 | _L | _S | _I | _R, 6 | _L | _S | _I | _R)
+              3 | _L | _S | _I, 6 | _L | _S | _I, 3 | _L | _S | _I | _R, 6 | _L | _S | _I | _R,
+              # and with most values in a dictionary
+              3 | _L | _S | _I | _K, 6 | _L | _S | _I | _K, 3 | _L | _S | _I | _K | _R,
+              6 | _L | _S | _I | _K | _R)
 _HERE = os.path.dirname(os.path.abspath(__file__))
 DEFAULT_CACHE = os.path.join(_HERE, "tuned_schedules.json")
 _memo: dict = {}
