@@ -7,25 +7,6 @@
 
 #include <vector>
 
-// Rows of a pool operator handled by one workgroup of the gradient kernel.
-#define GRAD_CHUNK_ROWS 1024
-#define GRAD_MAX_GROUP 8
-
-// One group of states that share a pool and a dimension (gradient kernel).
-struct GradGroup {
-    const vqe_csr *ops;        // device array of the pool's descriptors
-    int32_t M;
-    int32_t n_states;          // <= GRAD_MAX_GROUP
-    int32_t nchunks;
-    int32_t chunk_rows;
-    int64_t dim;
-    const void *psi[GRAD_MAX_GROUP];
-    const void *sigma[GRAD_MAX_GROUP];
-    double shift[GRAD_MAX_GROUP];
-    double *partials[GRAD_MAX_GROUP];   // per state: [M * nchunks]
-    double *g_out[GRAD_MAX_GROUP];      // per state: [M]
-};
-
 struct PairTable;
 struct MfTable;
 
@@ -351,12 +332,6 @@ void launch_sellt_layout(const vqe_csr *H, int32_t nt, int32_t tc, int E, uint16
 void launch_sellt_fill(const vqe_csr *H, int32_t nt, int32_t tc, int E, const uint16_t *srow,
                        const int2 *sslice, const int64_t *sbase, uint16_t *code, void *val,
                        uint32_t *smask, hipStream_t s);
-__global__ void k_energy_finalize(SpmvState single, const SpmvState *states, int n_states);
-
-void launch_pool_grad(int dtype, const GradGroup *groups, const int4 *tasks, unsigned grid,
-                      hipStream_t s);
-void launch_grad_finalize(const GradGroup *groups, const int2 *items, unsigned n_items,
-                          hipStream_t s);
 
 void launch_taylor_pair(int dtype, const TaylorState *states, const int2 *tasks, unsigned grid,
                         hipStream_t s);

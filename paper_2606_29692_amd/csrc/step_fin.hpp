@@ -25,6 +25,7 @@ __device__ __forceinline__ int step_fin_block(const SpmvState &hs, const ScreenS
     const int tid = threadIdx.x;
     if (tid < 64) {
         double re = 0.0, im = 0.0, n2 = 0.0;
+#pragma unroll 4
         for (int b = tid; b < hs.nblocks; b += 64) {
             re += hs.partials[(int64_t)b * 3 + 0];
             im += hs.partials[(int64_t)b * 3 + 1];

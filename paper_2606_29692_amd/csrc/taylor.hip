@@ -182,11 +182,19 @@ k_norm_partials(TaylorState single, const TaylorState *__restrict__ states,
     }
     const int64_t r0 = (int64_t)blk * NORM_ROWS_PER_BLOCK;
     const int64_t r1 = r0 + NORM_ROWS_PER_BLOCK < stp->dim ? r0 + NORM_ROWS_PER_BLOCK : stp->dim;
-    double s = 0.0;
-    for (int64_t r = r0 + threadIdx.x; r < r1; r += 256) {
-        const double2 p = Elem<DT>::ld(stp->psi, r);
-        s += p.x * p.x + p.y * p.y;
+    // a thread's rows loaded together (few blocks and one load in flight per
+    // thread is a chain of memory latencies), summed in order
+    constexpr int U = NORM_ROWS_PER_BLOCK / 256;
+    double2 p[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        const int64_t r = r0 + threadIdx.x + 256 * u;
+        p[u] = r < r1 ? Elem<DT>::ld(stp->psi, r) : make_double2(0.0, 0.0);
     }
+    double s = 0.0;
+#pragma unroll
+    for (int u = 0; u < U; u++)
+        s += p[u].x * p[u].x + p[u].y * p[u].y;
     __shared__ double red[4];
     s = wave_sum(s);
     if ((threadIdx.x & 63) == 0)
@@ -215,6 +223,17 @@ k_norm_scale(TaylorState single, const TaylorState *__restrict__ states,
         stp = &single;
         blk = blockIdx.x;
     }
+    // the block's rows load while the norm is summed
+    constexpr int U = NORM_ROWS_PER_BLOCK / 256;
+    const int64_t r0 = (int64_t)blk * NORM_ROWS_PER_BLOCK;
+    const int64_t r1 = r0 + NORM_ROWS_PER_BLOCK < stp->dim ? r0 + NORM_ROWS_PER_BLOCK : stp->dim;
+    double2 p[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        const int64_t r = r0 + threadIdx.x + 256 * u;
+        if (r < r1)
+            p[u] = Elem<DT>::ld(stp->psi, r);
+    }
     __shared__ double s_n2;
     if (threadIdx.x < 64) {
         double s = 0.0;
@@ -231,11 +250,11 @@ k_norm_scale(TaylorState single, const TaylorState *__restrict__ states,
     if (!stp->renorm)
         return;
     const double inv = 1.0 / sqrt(n2);
-    const int64_t r0 = (int64_t)blk * NORM_ROWS_PER_BLOCK;
-    const int64_t r1 = r0 + NORM_ROWS_PER_BLOCK < stp->dim ? r0 + NORM_ROWS_PER_BLOCK : stp->dim;
-    for (int64_t r = r0 + threadIdx.x; r < r1; r += 256) {
-        const double2 p = Elem<DT>::ld(stp->psi, r);
-        Elem<DT>::st(stp->psi, r, make_double2(p.x * inv, p.y * inv));
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        const int64_t r = r0 + threadIdx.x + 256 * u;
+        if (r < r1)
+            Elem<DT>::st(stp->psi, r, make_double2(p[u].x * inv, p[u].y * inv));
     }
 }
 
