@@ -522,7 +522,8 @@ VQE_API int vqe_batch_set_line_search(vqe_batch *plan, double theta_max);
  * are left unchanged.  Every generator of every pool must satisfy
  * A[r,c] A[c,r] = -1 on its pairs (VQE_ENOTSUP otherwise).  Allocates nine
  * state vectors per slot on the first call (VQE_ENOMEM); synchronises the
- * stream once to upload the call's descriptors, otherwise asynchronous.
+ * stream once to upload descriptors that differ from the last call's, otherwise
+ * asynchronous.
  * Errors: VQE_EINVAL (null plan arrays, n > ld, bad theta_max or sweeps).
  */
 VQE_API int vqe_batch_reoptimize(vqe_batch *plan, const int32_t *ks, double *thetas, int32_t ld,

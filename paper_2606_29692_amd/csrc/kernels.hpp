@@ -124,7 +124,9 @@ struct MfTable {
 #define MF_TAB_ITER (64 + 4)
 
 // One state of the line search over the selected generator's angle.
-#define LS_ROWS_PER_BLOCK 2048
+// (512: 16 states of 14 qubits are 512 workgroups; blocks of 2048 rows left half
+// the CUs without one and each thread a chain of eight rows)
+#define LS_ROWS_PER_BLOCK 512
 #define LS_NVEC 7             // partial sums of the vector kernel
 #define LS_GRID 256           // angles of the coarse search
 struct LsState {
@@ -156,6 +158,7 @@ struct LsState {
 #define RO_NDOT 12            // partial sums of the inner-product kernel
 struct RoState {
     void *psi;                // out: the slot's state at the final angles
+    const void *ref;          // the reference state
     void *L;                  // the state before the visited update
     void *v1, *v2;            // A L, A^2 L
     void *w[3];               // (L, A L, A^2 L) with the later updates applied
@@ -177,6 +180,7 @@ void launch_ls_vectors(int dtype, const LsState *states, const int2 *tasks, unsi
                        hipStream_t s);
 void launch_ls_dot(int dtype, const LsState *states, const int2 *tasks, unsigned grid,
                    hipStream_t s);
+void launch_ro_start(int dtype, const RoState *states, const int2 *tasks, unsigned grid, hipStream_t s);
 void launch_ro_vectors(int dtype, const RoState *states, const int2 *tasks, unsigned grid, int m,
                        hipStream_t s);
 void launch_ro_taylor(int dtype, const RoState *states, const int2 *tasks, unsigned grid, int m,

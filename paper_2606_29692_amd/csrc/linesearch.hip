@@ -13,7 +13,7 @@
 // The plan builds v1 = A psi and v2 = A^2 psi (pair by pair), takes the two
 // products S v1 and S v2 with its H-product schedule, reduces the entries in
 // FP64 and minimises E over [-theta_max, theta_max]: the best of a 256-point
-// grid, refined by golden-section search on the grid interval around it.
+// grid, refined on the grid interval around it.
 #include "kernels.hpp"
 
 namespace {
@@ -161,13 +161,42 @@ __device__ __forceinline__ double wave_total(const double *p, int n, int stride,
     return wave_sum(v);
 }
 
+// The lane with the lowest energy (then the lowest index), its values in every lane.
+__device__ __forceinline__ void wave_argmin(double &e, int &i)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const double eo = __shfl_xor(e, o, 64);
+        const int io = __shfl_xor(i, o, 64);
+        if (eo < e || (eo == e && io < i)) {
+            e = eo;
+            i = io;
+        }
+    }
+}
+
+// The lowest of 64 lanes' energies, in every lane (lane moves within 16 lanes,
+// two shuffles beyond).
+__device__ __forceinline__ double wave_min(double e)
+{
+    e = fmin(e, dpp_f64<0xB1>(e));
+    e = fmin(e, dpp_f64<0x4E>(e));
+    e = fmin(e, dpp_f64<0x141>(e));
+    e = fmin(e, dpp_f64<0x140>(e));
+    e = fmin(e, __shfl_xor(e, 16, 64));
+    return fmin(e, __shfl_xor(e, 32, 64));
+}
+
 // Minimiser of E(theta) over [-tm, tm]: the lowest point of an LS_GRID-point
 // grid (lane l evaluates points l, l + 64, ...; ties to the lower index),
-// refined by golden-section search on the neighbouring grid interval (every
-// lane runs the same arithmetic); t_alt wins when nothing is lower.
+// then LS_ROUNDS times the lowest of 64 points that cut the interval around it
+// into 65 parts, whose neighbours bound the next interval: to 3e-11 of the
+// grid's step, where the rounding of E leaves a minimum flat over some 1e-8.  (80
+// golden-section steps are a chain of 80 evaluations: 22.7 us a launch against
+// 9.0.)  t_alt wins when nothing is lower.
+#define LS_ROUNDS 7
 __device__ double ls_minimise(const LsForms &f, double tm, int lane, double t_alt)
 {
-    // coarse grid: lane l evaluates points l, l + 64, l + 128, l + 192
     const double step = 2.0 * tm / (double)(LS_GRID - 1);
     double best = 0.0;
     int bi = -1;
@@ -178,36 +207,19 @@ __device__ double ls_minimise(const LsForms &f, double tm, int lane, double t_al
             bi = i;
         }
     }
-    // wave argmin (lowest energy, then lowest index)
-    for (int o = 32; o > 0; o >>= 1) {
-        const double eo = __shfl_xor(best, o, 64);
-        const int io = __shfl_xor(bi, o, 64);
-        if (eo < best || (eo == best && io < bi)) {
-            best = eo;
-            bi = io;
-        }
-    }
-    // golden-section refinement on the neighbouring grid interval (every lane
-    // runs the same arithmetic)
+    wave_argmin(best, bi);
     double lo = -tm + step * (bi > 0 ? bi - 1 : 0);
     double hi = -tm + step * (bi < LS_GRID - 1 ? bi + 1 : LS_GRID - 1);
-    const double gr = 0.6180339887498949;
-    double x1 = hi - gr * (hi - lo), x2 = lo + gr * (hi - lo);
-    double f1 = ls_energy(f, x1), f2 = ls_energy(f, x2);
-    for (int it = 0; it < 80; it++) {
-        if (f1 <= f2) {
-            hi = x2;
-            x2 = x1;
-            f2 = f1;
-            x1 = hi - gr * (hi - lo);
-            f1 = ls_energy(f, x1);
-        } else {
-            lo = x1;
-            x1 = x2;
-            f1 = f2;
-            x2 = lo + gr * (hi - lo);
-            f2 = ls_energy(f, x2);
-        }
+    for (int it = 0; it < LS_ROUNDS; it++) {
+        const double h = (hi - lo) * (1.0 / 65.0);
+        const double e = ls_energy(f, lo + h * (lane + 1));
+        const uint64_t m = __ballot(e == wave_min(e));
+        const int i = m ? __ffsll((unsigned long long)m) - 1 : 0;
+        const double l0 = lo;
+        if (i > 0)
+            lo = l0 + h * i;
+        if (i < 63)
+            hi = l0 + h * (i + 2);
     }
     double t_best = -tm + step * bi, e_best = best;
     const double xm = 0.5 * (lo + hi), em = ls_energy(f, xm);
@@ -310,6 +322,21 @@ __device__ __forceinline__ bool ro_valid(const RoState &st, int m)
 {
     const int32_t k = gmem(st.ks)[m];
     return k >= 0 && k < st.M;
+}
+
+// L <- ref: every sweep starts from the reference.
+template <int DT>
+__global__ void __launch_bounds__(256)
+k_ro_start(const RoState *__restrict__ states, const int2 *__restrict__ tasks)
+{
+    const int2 task = tasks[blockIdx.x];
+    if (task.x < 0)
+        return;
+    const RoState &st = states[task.x];
+    const int64_t r0 = (int64_t)task.y * LS_ROWS_PER_BLOCK;
+    const int64_t r1 = r0 + LS_ROWS_PER_BLOCK < st.dim ? r0 + LS_ROWS_PER_BLOCK : st.dim;
+    for (int64_t r = r0 + threadIdx.x; r < r1; r += 256)
+        Elem<DT>::st(st.L, r, Elem<DT>::ld(st.ref, r));
 }
 
 // v1 = A_m L, v2 = A_m^2 L over a block of rows; w = (L, v1, v2).
@@ -516,6 +543,14 @@ void launch_ls_dot(int dtype, const LsState *states, const int2 *tasks, unsigned
 void launch_ls_solve(const LsState *states, unsigned n_states, hipStream_t s)
 {
     k_ls_solve<<<n_states, 64, 0, s>>>(states, (int)n_states);
+}
+
+void launch_ro_start(int dtype, const RoState *states, const int2 *tasks, unsigned grid, hipStream_t s)
+{
+    if (dtype == VQE_C128)
+        k_ro_start<VQE_C128><<<grid, 256, 0, s>>>(states, tasks);
+    else
+        k_ro_start<VQE_C64><<<grid, 256, 0, s>>>(states, tasks);
 }
 
 void launch_ro_vectors(int dtype, const RoState *states, const int2 *tasks, unsigned grid, int m,
