@@ -238,6 +238,9 @@ struct vqe_batch {
     std::vector<const vqe_mf_desc *> mf_desc_dev;  // mf mode: device descriptors of each table
     std::vector<int> table_idx;                    // table of each slot
     std::vector<int> xcd;                          // XCD of each slot
+    bool spread = false;                           // tasks round all XCDs instead (few states)
+    // XCD of the i-th task of slot s in a task list
+    int home(int s, size_t i) const { return spread ? (int)((xcd[s] + i) % 8) : xcd[s]; }
     int ls_checked = 0;                            // 0 unknown, 1 every generator has A^3 = -A, -1 not
     bool ls_ready = false;
     char *ls_mem = nullptr;
@@ -809,6 +812,21 @@ extern "C" int vqe_batch_create(vqe_ctx *ctx, int32_t B, const vqe_batch_item *i
         xcd_of[s] = x;
         load[x] += (double)items[s].H->nnz * 12.0 + (double)items[s].H->dim * 20.0;
     }
+    // A state on one XCD keeps its vectors in one L2, but few states leave XCDs
+    // idle.  When the fullest has over 1.25 times its share and a state is of 2^14
+    // rows or more, every state's tasks go round all XCDs: a step of 2 states of
+    // 18 qubits 1276 -> 540 us, of 2 of 16 qubits 219 -> 179, of 1 of 14 qubits
+    // 43 -> 35; of smaller states it would lose (3 of 8 qubits 15.5 -> 17.0, 5 of
+    // 10 qubits 17.1 -> 18.8).
+    const double share = std::accumulate(load.begin(), load.end(), 0.0) / kXcd;
+    const int64_t top_dim = [&] {
+        int64_t d = 0;
+        for (int s = 0; s < B; s++)
+            d = std::max<int64_t>(d, items[s].H->dim);
+        return d;
+    }();
+    p->spread = top_dim >= 16384 && *std::max_element(load.begin(), load.end()) > 1.25 * share;
+    p->xcd = xcd_of;
 
     Arena A;
     const size_t o_spmv = A.take(sizeof(SpmvState) * B);
@@ -871,19 +889,19 @@ extern "C" int vqe_batch_create(vqe_ctx *ctx, int32_t B, const vqe_batch_item *i
             const int64_t rb = (lanes[s] & VQE_SPMV_SLICED) ? SPMV_SELLT_ROWS : SPMV_BLK_ROWS;
             const int nb = (int)((dim + rb - 1) / rb);
             for (int b = 0; b < nb; b++)
-                per[xcd_of[s]].push_back(make_int2(s, b));
+                per[p->home(s, b)].push_back(make_int2(s, b));
             continue;
         }
         if (lanes[s] & VQE_SPMV_TILED) {
             const int nb = (int)((dim + SPMV_LDS_ROWS - 1) / SPMV_LDS_ROWS);
             for (int b = 0; b < nb; b++)
                 for (int t = 0; t < ntiles[s]; t++)
-                    per[xcd_of[s]].push_back(make_int2(s, (b << 8) | t));
+                    per[p->home(s, b)].push_back(make_int2(s, (b << 8) | t));
             auto &ps = per_sum[lanes[s]];
             if (ps.empty())
                 ps.resize(kXcd);
             for (int b = 0; b < (int)((dim + SPMV_SUM_ROWS - 1) / SPMV_SUM_ROWS); b++)
-                ps[xcd_of[s]].push_back(make_int2(s, b));
+                ps[p->home(s, b)].push_back(make_int2(s, b));
             bounds_range[s] = {(unsigned)bounds_list.size(), (unsigned)((dim + 255) / 256)};
             for (int b = 0; b < (int)((dim + 255) / 256); b++)
                 bounds_list.push_back(make_int2(s, b));
@@ -894,11 +912,11 @@ extern "C" int vqe_batch_create(vqe_ctx *ctx, int32_t B, const vqe_batch_item *i
             // (first part << 3) | parts, each task within a block of rows
             const int np = parts[lanes[s]];
             for (int b = 0; b < nb; b += np)
-                per[xcd_of[s]].push_back(make_int2(s, b << 3 | np));
+                per[p->home(s, b / np)].push_back(make_int2(s, b << 3 | np));
             continue;
         }
         for (int b = 0; b < nb; b++)
-            per[xcd_of[s]].push_back(make_int2(s, b));
+            per[p->home(s, b)].push_back(make_int2(s, b));
     }
     std::vector<std::pair<int, size_t>> spmv_tab;
     std::vector<std::vector<int2>> spmv_lists, sum_lists;
@@ -1073,20 +1091,25 @@ extern "C" int vqe_batch_create(vqe_ctx *ctx, int32_t B, const vqe_batch_item *i
     const size_t o_screen = A.take(sizeof(ScreenState) * B);
     std::vector<std::vector<int4>> screen_per(kXcd);
     const int n_ranges = 2;
+    // workgroups per state that fill the CUs, at most 16 where a state is small
+    // (5 of 10 qubits: 51 a state 20.9 us a step, 16 17.1 us)
+    const double wg = std::min((double)ctx->n_cu / B, top_dim >= 16384 ? (double)ctx->n_cu : 16.0);
     for (int s = 0; s < B; s++) {
         const int ti = table_of[pool_key(items[s].pool)];
         const PairTable &tb = tables[ti];
         const int M = tb.M;
+        size_t i = 0;
         if (mf_mode) {
-            // about eight workgroups per state, split over the lists by work
+            // about eight workgroups per state, or as many as CUs for few
+            // states, split over the lists by work
             const MfHostPlan &hp = mf_plans[ti];
             double W = 0.0;
             for (auto &L : hp.list_info)
                 W += L.work;
             for (auto &L : hp.list_info) {
-                const int nr = std::max(1, std::min({L.len, 255, (int)std::lround(8.0 * L.work / W)}));
+                const int nr = std::max(1, std::min({L.len, 255, (int)std::lround(std::max(8.0, wg) * L.work / W)}));
                 for (int r = 0; r < nr; r++)
-                    screen_per[xcd_of[s]].push_back(make_int4(s, L.off, L.len, r | (nr << 8) | (L.v << 16)));
+                    screen_per[p->home(s, i++)].push_back(make_int4(s, L.off, L.len, r | (nr << 8) | (L.v << 16)));
             }
             const size_t elem = 2 * vqe_elem_bytes(dtype);
             p->screen_lds = std::max(p->screen_lds, (size_t)hp.tile_rows * elem);
@@ -1094,7 +1117,7 @@ extern "C" int vqe_batch_create(vqe_ctx *ctx, int32_t B, const vqe_batch_item *i
             const int nr = std::min(n_ranges, M);
             for (int t = 0; t < tb.nt; t++)
                 for (int r = 0; r < nr; r++)
-                    screen_per[xcd_of[s]].push_back(make_int4(s, t, r, nr));
+                    screen_per[p->home(s, i++)].push_back(make_int4(s, t, r, nr));
             const int64_t rows = std::min<int64_t>(tb.tile_rows, items[s].H->dim);
             p->screen_lds = std::max(p->screen_lds, (size_t)(2 * rows * vqe_elem_bytes(dtype)));
         }
@@ -1103,21 +1126,22 @@ extern "C" int vqe_batch_create(vqe_ctx *ctx, int32_t B, const vqe_batch_item *i
     auto screen_flat = interleave(screen_per, make_int4(-1, 0, 0, 0));
     const size_t o_stasks = A.take(screen_flat.size() * sizeof(int4));
     // real-state screen: four workgroups per state (one per CU for 64
-    // states), generators dealt over them by descending cost; a complex state
+    // states; more of them for fewer states, up to 16), generators dealt over them by descending cost; a complex state
     // runs the tiled screen's lists in the same workgroups, so the LDS holds
     // either form
     std::vector<std::vector<int4>> screen1_per(kXcd);
-    // (ADAPTVQE_SCREEN_WG overrides the four, 1..64, for tuning)
-    int split = 4;
+    // (ADAPTVQE_SCREEN_WG overrides it, 1..64, for tuning)
+    int split = std::max(4, std::min(16, (int)wg));
     if (const char *e = std::getenv("ADAPTVQE_SCREEN_WG"))
         split = std::max(1, std::min(64, std::atoi(e)));
     if (real_screen)
         for (int s = 0; s < B; s++) {
             const MfHostPlan &hp1 = mf_plans1[table_of[pool_key(items[s].pool)]];
+            size_t i = 0;
             for (auto &L : hp1.list_info) {
                 const int nr = std::max(1, std::min(L.len, split));
                 for (int r = 0; r < nr; r++)
-                    screen1_per[xcd_of[s]].push_back(make_int4(s, L.off, L.len, r | (nr << 8)));
+                    screen1_per[p->home(s, i++)].push_back(make_int4(s, L.off, L.len, r | (nr << 8)));
             }
             p->screen1_lds = std::max({p->screen1_lds, screen_real_lds(items[s].H->dim, dtype),
                                        p->screen_lds});
@@ -1154,14 +1178,14 @@ extern "C" int vqe_batch_create(vqe_ctx *ctx, int32_t B, const vqe_batch_item *i
                            : (int)((dim + TAYLOR_ROWS_PER_BLOCK - 1) / TAYLOR_ROWS_PER_BLOCK);
         const int nn = (int)((dim + NORM_ROWS_PER_BLOCK - 1) / NORM_ROWS_PER_BLOCK);
         for (int b = 0; b < nt; b++)
-            tay_per[xcd_of[s]].push_back(make_int2(s, b));
+            tay_per[p->home(s, b)].push_back(make_int2(s, b));
         if (mf_mode) {
             // the update blocks' changes of |psi|^2, for the renormalisation
             o_taypart[s] = A.take((size_t)nt * sizeof(double));
             ntay[s] = nt;
         }
         for (int b = 0; b < nn; b++)
-            norm_per[xcd_of[s]].push_back(make_int2(s, b));
+            norm_per[p->home(s, b)].push_back(make_int2(s, b));
     }
     auto tay_flat = interleave(tay_per, make_int2(-1, 0));
     auto norm_flat = interleave(norm_per, make_int2(-1, 0));
@@ -1281,7 +1305,6 @@ extern "C" int vqe_batch_create(vqe_ctx *ctx, int32_t B, const vqe_batch_item *i
         p->pool_ops.push_back(pool_key(items[s].pool));
         p->dims.push_back(items[s].H->dim);
         p->table_idx.push_back(table_of[pool_key(items[s].pool)]);
-        p->xcd.push_back(xcd_of[s]);
     }
     p->tables_host = tables;
     for (const PairTable &t : tables)
@@ -1876,7 +1899,7 @@ extern "C" int vqe_batch_set_line_search(vqe_batch *p, double theta_max)
         for (int s = 0; s < B; s++) {
             const int nb = (int)((p->dims[s] + LS_ROWS_PER_BLOCK - 1) / LS_ROWS_PER_BLOCK);
             for (int b = 0; b < nb; b++)
-                per[p->xcd[s]].push_back(make_int2(s, b));
+                per[p->home(s, b)].push_back(make_int2(s, b));
         }
         auto flat = interleave(per, make_int2(-1, 0));
         const size_t o_tasks = A.take(flat.size() * sizeof(int2));
@@ -1968,7 +1991,7 @@ extern "C" int vqe_batch_reoptimize(vqe_batch *p, const int32_t *ks, double *the
         for (int s = 0; s < B; s++) {
             const int nb = (int)((p->dims[s] + LS_ROWS_PER_BLOCK - 1) / LS_ROWS_PER_BLOCK);
             for (int b = 0; b < nb; b++)
-                per[p->xcd[s]].push_back(make_int2(s, b));
+                per[p->home(s, b)].push_back(make_int2(s, b));
         }
         auto flat = interleave(per, make_int2(-1, 0));
         const size_t o_tasks = A.take(flat.size() * sizeof(int2));
