@@ -208,6 +208,9 @@ struct vqe_batch {
     hipGraphExec_t exec[32] = {};  // rest-of-step graphs by flag set (step_key)
     hipGraph_t graph[32] = {};
     bool compact_taylor = false;   // every pool has a compact pair table
+    // CSR pools and states of at most NORM_ROWS_PER_BLOCK rows: update, norm and
+    // rescale in one launch, which also takes the angles' row
+    bool small_taylor = false;
     bool mf = false;               // every pool is matrix-free: screen and update from records
     // host image of the descriptors (for rebinding slots)
     std::vector<char> image;
@@ -584,7 +587,7 @@ int enqueue_spmv(vqe_batch *p)
     return VQE_OK;
 }
 
-// theta_row (nullable, matrix-free plans): the update's angles from this
+// theta_row (nullable; matrix-free plans and small states): the update's angles from this
 // device row instead of the plan's angle buffer (which the update then sets)
 int enqueue_rest(vqe_batch *p, uint32_t flags, hipEvent_t *ev, const double *theta_row = nullptr)
 {
@@ -636,13 +639,16 @@ int enqueue_rest(vqe_batch *p, uint32_t flags, hipEvent_t *ev, const double *the
                                  p->rel_tie, theta_row, s);
         else if (p->mf)
             launch_taylor_mf(p->dtype, p->d_tay, p->d_tay_tasks, p->n_tay_tasks, theta_row, s);
+        else if (p->small_taylor)
+            launch_taylor_small(p->dtype, p->d_tay, (unsigned)p->B, p->compact_taylor,
+                                (flags & VQE_STEP_RENORM) != 0, theta_row, s);
         else if (p->compact_taylor)
             launch_taylor_compact(p->dtype, p->d_tay, p->d_tay_tasks, p->n_tay_tasks, s);
         else
             launch_taylor_pair(p->dtype, p->d_tay, p->d_tay_tasks, p->n_tay_tasks, s);
     }
     rc = rc ? rc : mark(5);
-    if (!(flags & VQE_STEP_NO_UPDATE) && (flags & VQE_STEP_RENORM)) {
+    if (!(flags & VQE_STEP_NO_UPDATE) && (flags & VQE_STEP_RENORM) && !p->small_taylor) {
         if (p->mf)
             launch_norm_mf(p->dtype, p->d_tay, p->d_norm_tasks, p->n_norm_tasks, s);
         else
@@ -1167,6 +1173,7 @@ extern "C" int vqe_batch_create(vqe_ctx *ctx, int32_t B, const vqe_batch_item *i
         for (int j = 0; j < tb.M; j++)
             max_pairs[i] = std::max(max_pairs[i], pts[(size_t)(j + 1) * tb.nt] - pts[(size_t)j * tb.nt]);
     }
+    p->small_taylor = !mf_mode && top_dim <= NORM_ROWS_PER_BLOCK;
     std::vector<std::vector<int2>> tay_per(kXcd), norm_per(kXcd);
     std::vector<size_t> o_taypart(B, 0);
     std::vector<int32_t> ntay(B, 0);
@@ -1608,7 +1615,7 @@ extern "C" int vqe_batch_run(vqe_batch *p, uint32_t flags, const double *theta_r
             int rc;
             if (ls) {
                 rc = enqueue_step(p, sflags);
-            } else if (p->mf) {
+            } else if (p->mf || p->small_taylor) {
                 rc = enqueue_spmv(p);
                 rc = rc ? rc : enqueue_rest(p, sflags, nullptr, row);
             } else {

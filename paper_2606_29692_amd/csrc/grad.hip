@@ -20,7 +20,8 @@ constexpr int GRAD_ROWS = 4, GRAD_THREADS = 256, GRAD_CHUNK = GRAD_ROWS * GRAD_T
 template <int DT>
 __global__ void __launch_bounds__(GRAD_THREADS)
 k_pool_grad(const vqe_csr *__restrict__ ops, const void *__restrict__ psi,
-            const void *__restrict__ sigma, double shift, int64_t dim, double *__restrict__ partials)
+            const void *__restrict__ sigma, double shift, int64_t dim, double *__restrict__ partials,
+            double *__restrict__ g_out)
 {
     constexpr int nt = GRAD_THREADS;
     const int j = blockIdx.y;
@@ -95,8 +96,13 @@ k_pool_grad(const vqe_csr *__restrict__ ops, const void *__restrict__ psi,
     if ((threadIdx.x & 63) == 0)
         s_red[threadIdx.x >> 6] = acc;
     __syncthreads();
-    if (threadIdx.x == 0)
-        partials[(int64_t)j * gridDim.x + blockIdx.x] = ((s_red[0] + s_red[1]) + s_red[2]) + s_red[3];
+    if (threadIdx.x == 0) {
+        const double v = ((s_red[0] + s_red[1]) + s_red[2]) + s_red[3];
+        if (gridDim.x == 1)
+            g_out[j] = 2.0 * v;      // the only chunk: no second launch
+        else
+            partials[(int64_t)j * gridDim.x + blockIdx.x] = v;
+    }
 }
 
 // g_j from its chunks' sums, one thread per generator.
@@ -186,9 +192,11 @@ int vqe_pool_grad_launch(vqe_ctx *ctx, const vqe_csr *H, const vqe_pool *pool, c
     for (int j0 = 0; j0 < M; j0 += 65535) {
         const int m = M - j0 < 65535 ? M - j0 : 65535;
         k<<<dim3((unsigned)nchunks, (unsigned)m), GRAD_THREADS, 0, ctx->stream>>>(
-            pool->ops + j0, psi, sigma, H->diag_shift, dim, (double *)ws + (size_t)j0 * nchunks);
+            pool->ops + j0, psi, sigma, H->diag_shift, dim, (double *)ws + (size_t)j0 * nchunks,
+            g_out + j0);
     }
-    k_grad_fin<<<(unsigned)((M + 63) / 64), 64, 0, ctx->stream>>>((const double *)ws, M, nchunks, g_out);
+    if (nchunks > 1)
+        k_grad_fin<<<(unsigned)((M + 63) / 64), 64, 0, ctx->stream>>>((const double *)ws, M, nchunks, g_out);
     VQE_LAUNCH_CHECK(ctx);
     return VQE_OK;
 }

@@ -341,5 +341,9 @@ void launch_taylor_pair(int dtype, const TaylorState *states, const int2 *tasks,
                         hipStream_t s);
 void launch_norm(int dtype, const TaylorState *states, const int2 *tasks, unsigned grid,
                  hipStream_t s);
+// update and (renorm) rescale of every state by one workgroup each: states of at
+// most NORM_ROWS_PER_BLOCK rows
+void launch_taylor_small(int dtype, const TaylorState *states, unsigned n_states, bool compact, bool renorm,
+                         const double *theta_row, hipStream_t s);
 void launch_taylor_compact(int dtype, const TaylorState *states, const int2 *tasks,
                            unsigned grid, hipStream_t s);

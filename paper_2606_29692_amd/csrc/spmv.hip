@@ -97,35 +97,21 @@ template <int DT> struct RowLoad<DT, 4> {
     }
 };
 
-template <int DT, int L, int V, bool BATCH>
-__global__ void __launch_bounds__(256)
-k_spmv_energy(SpmvState single, const SpmvState *__restrict__ states,
-              const int2 *__restrict__ tasks)
+// Wave wid (of four) of block blk: its rows of sigma, and its sums of the
+// energy terms (each over the whole wave).
+template <int DT, int L, int V>
+__device__ __forceinline__ void spmv_energy_rows(const SpmvState &st, int blk, int wid, int lane, double &e_re,
+                                                 double &e_im, double &e_n2)
 {
-    SpmvState st;
-    int blk;
-    if (BATCH) {
-        int2 t = tasks[blockIdx.x];
-        if (t.x < 0)
-            return;
-        st = states[t.x];
-        blk = t.y;
-        if (VQE_SKIP(st))
-            return;
-    } else {
-        st = single;
-        blk = blockIdx.x;
-    }
     constexpr int G = VQE_WAVE / L;
     constexpr int RPB = spmv_rows_per_block(L);
     constexpr int U = V == 1 ? 4 : 1;     // passes issued together
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int sub = lane / L, sl = lane % L;
     const int32_t *__restrict__ rowptr = st.rowptr;
     const int32_t *__restrict__ col = st.col;
     using T = typename Elem<DT>::T;
     const T *__restrict__ val = reinterpret_cast<const T *>(st.val);
-    double e_re = 0.0, e_im = 0.0, e_n2 = 0.0;
+    e_re = e_im = e_n2 = 0.0;
 #pragma unroll
     for (int it = 0; it < SPMV_RPT; it++) {
         const int64_t r = (int64_t)blk * RPB + (it * 4 + wid) * G + sub;
@@ -161,10 +147,34 @@ k_spmv_energy(SpmvState single, const SpmvState *__restrict__ states,
             e_n2 += p.x * p.x + p.y * p.y;
         }
     }
-    __shared__ double s_part[4][3];
     e_re = wave_sum(e_re);
     e_im = wave_sum(e_im);
     e_n2 = wave_sum(e_n2);
+}
+
+template <int DT, int L, int V, bool BATCH>
+__global__ void __launch_bounds__(256)
+k_spmv_energy(SpmvState single, const SpmvState *__restrict__ states,
+              const int2 *__restrict__ tasks)
+{
+    SpmvState st;
+    int blk;
+    if (BATCH) {
+        int2 t = tasks[blockIdx.x];
+        if (t.x < 0)
+            return;
+        st = states[t.x];
+        blk = t.y;
+        if (VQE_SKIP(st))
+            return;
+    } else {
+        st = single;
+        blk = blockIdx.x;
+    }
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    double e_re, e_im, e_n2;
+    spmv_energy_rows<DT, L, V>(st, blk, wid, lane, e_re, e_im, e_n2);
+    __shared__ double s_part[4][3];
     if (lane == 0) {
         s_part[wid][0] = e_re;
         s_part[wid][1] = e_im;
@@ -175,6 +185,45 @@ k_spmv_energy(SpmvState single, const SpmvState *__restrict__ states,
         const int q = threadIdx.x;
         const double v = ((s_part[0][q] + s_part[1][q]) + s_part[2][q]) + s_part[3][q];
         gmem(st.partials)[(int64_t)blk * 3 + q] = v;
+    }
+}
+
+// A small single state in one workgroup, product, block sums and energy (the
+// same sums as k_spmv_energy and k_energy_finalize): up to SPMV_SMALL_DIM rows a
+// call is two launches' cost on the host rather than work (9.6 us a call, one
+// launch 6.3 us at 4 and 6 qubits, 7.6 us at 8).
+#define SPMV_SMALL_DIM 256
+template <int DT, int L>
+__global__ void __launch_bounds__(1024)
+k_spmv_energy_small(SpmvState st)
+{
+    constexpr int NB = (SPMV_SMALL_DIM + spmv_rows_per_block(L) - 1) / spmv_rows_per_block(L);
+    static_assert(NB <= VQE_WAVE, "a block sum per lane");
+    __shared__ double s_part[NB][4][3], s_sum[3];
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    for (int b = wid >> 2; b < st.nblocks; b += 4) {
+        double e_re, e_im, e_n2;
+        spmv_energy_rows<DT, L, 1>(st, b, wid & 3, lane, e_re, e_im, e_n2);
+        if (lane == 0) {
+            s_part[b][wid & 3][0] = e_re;
+            s_part[b][wid & 3][1] = e_im;
+            s_part[b][wid & 3][2] = e_n2;
+        }
+    }
+    __syncthreads();
+    if (wid < 3) {
+        double v = 0.0;
+        if (lane < st.nblocks)
+            v = ((s_part[lane][0][wid] + s_part[lane][1][wid]) + s_part[lane][2][wid]) + s_part[lane][3][wid];
+        v = wave_sum(v);
+        if (lane == 0)
+            s_sum[wid] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0 && st.energy_out) {
+        st.energy_out[0] = st.shift + s_sum[0] / s_sum[2];
+        st.energy_out[1] = s_sum[2];
+        st.energy_out[2] = s_sum[1];
     }
 }
 
@@ -3740,6 +3789,19 @@ int vqe_spmv_energy_core(vqe_ctx *ctx, const vqe_csr *H, const void *psi, void *
     st.nblocks = (int32_t)nblk;
     st.lanes = lanes;
     st.nnz = H->nnz;
+    if (dim <= SPMV_SMALL_DIM && (lanes == 8 || lanes == 16 || lanes == 32 || lanes == 64)) {
+        auto pick = [&](auto k8, auto k16, auto k32, auto k64) {
+            return lanes == 8 ? k8 : lanes == 16 ? k16 : lanes == 32 ? k32 : k64;
+        };
+        auto k = H->dtype == VQE_C128
+                     ? pick(k_spmv_energy_small<VQE_C128, 8>, k_spmv_energy_small<VQE_C128, 16>,
+                            k_spmv_energy_small<VQE_C128, 32>, k_spmv_energy_small<VQE_C128, 64>)
+                     : pick(k_spmv_energy_small<VQE_C64, 8>, k_spmv_energy_small<VQE_C64, 16>,
+                            k_spmv_energy_small<VQE_C64, 32>, k_spmv_energy_small<VQE_C64, 64>);
+        k<<<1, 1024, 0, ctx->stream>>>(st);
+        VQE_LAUNCH_CHECK(ctx);
+        return VQE_OK;
+    }
     launch_spmv(H->dtype, lanes, st, nullptr, nullptr, (unsigned)nblk, ctx->stream, dim);
     k_energy_finalize<<<1, 192, 0, ctx->stream>>>(st);
     VQE_LAUNCH_CHECK(ctx);

@@ -34,55 +34,19 @@ __device__ __forceinline__ double2 cmul(double2 a, double2 b)
     return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
 
-template <int DT, bool BATCH>
-__global__ void __launch_bounds__(TAYLOR_ROWS_PER_BLOCK)
-k_taylor_pair(TaylorState single, const TaylorState *__restrict__ states,
-              const int2 *__restrict__ tasks)
+// The update of row r's pair by its owner, the lower row.
+template <int DT>
+__device__ __forceinline__ void taylor_pair_row(const int32_t *rowptr, const int32_t *col, const void *val,
+                                                double theta, void *psi, int64_t r)
 {
-    int blk;
-    const TaylorState *stp;
-    if (BATCH) {
-        const int2 t = tasks[blockIdx.x];
-        if (t.x < 0)
-            return;
-        stp = states + t.x;
-        blk = t.y;
-        if (VQE_SKIP(*stp))
-            return;
-    } else {
-        stp = &single;
-        blk = blockIdx.x;
-    }
-    const int64_t r = (int64_t)blk * TAYLOR_ROWS_PER_BLOCK + threadIdx.x;
-    const int64_t dim = stp->dim;
-    if (r >= dim)
-        return;
-    const int32_t *rowptr;
-    const int32_t *col;
-    const void *val;
-    if (stp->k) {
-        const int32_t kk = *stp->k;
-        if (kk < 0 || kk >= stp->M)
-            return;
-        const vqe_csr *op = stp->ops + kk;
-        rowptr = op->rowptr;
-        col = op->col;
-        val = op->val;
-    } else {
-        rowptr = stp->op.rowptr;
-        col = stp->op.col;
-        val = stp->op.val;
-    }
     const int k0 = gmem(rowptr)[r];
     if (gmem(rowptr)[r + 1] - k0 != 1)
         return;
     const int64_t c = gmem(col)[k0];
     if (c < r)
         return;   // the partner row owns the pair
-    const double theta = stp->theta ? *stp->theta : stp->theta_value;
     double cf[6];
     taylor_coeffs(theta, cf);
-    void *psi = stp->psi;
     const double2 a = Elem<DT>::ld(val, k0);
     if (c == r) {
         // 1x1 block: v_n = a^n psi_r
@@ -115,8 +79,70 @@ k_taylor_pair(TaylorState single, const TaylorState *__restrict__ states,
     Elem<DT>::st(psi, c, ac);
 }
 
+template <int DT, bool BATCH>
+__global__ void __launch_bounds__(TAYLOR_ROWS_PER_BLOCK)
+k_taylor_pair(TaylorState single, const TaylorState *__restrict__ states,
+              const int2 *__restrict__ tasks)
+{
+    int blk;
+    const TaylorState *stp;
+    if (BATCH) {
+        const int2 t = tasks[blockIdx.x];
+        if (t.x < 0)
+            return;
+        stp = states + t.x;
+        blk = t.y;
+        if (VQE_SKIP(*stp))
+            return;
+    } else {
+        stp = &single;
+        blk = blockIdx.x;
+    }
+    const int64_t r = (int64_t)blk * TAYLOR_ROWS_PER_BLOCK + threadIdx.x;
+    if (r >= stp->dim)
+        return;
+    const vqe_csr *op = &stp->op;
+    if (stp->k) {
+        const int32_t kk = *stp->k;
+        if (kk < 0 || kk >= stp->M)
+            return;
+        op = stp->ops + kk;
+    }
+    taylor_pair_row<DT>(op->rowptr, op->col, op->val, stp->theta ? *stp->theta : stp->theta_value,
+                        stp->psi, r);
+}
+
+// Pair p of the compact pair table for generator k: {r, c = r ^ x_k}, entries +-1.
+template <int DT>
+__device__ __forceinline__ void taylor_compact_pair(const PairTable *tb, int32_t k, int p, double theta,
+                                                    void *psi)
+{
+    const uint32_t w = gmem(tb->words)[p];
+    const int64_t r = w & 0x3fffffffu;
+    const int64_t c = r ^ (int64_t)gmem(tb->xmask)[k];
+    const double sa = (w >> 30) & 1u ? -1.0 : 1.0;   // A[r,c]
+    const double sb = (w >> 31) ? -1.0 : 1.0;         // A[c,r]
+    double cf[6];
+    taylor_coeffs(theta, cf);
+    double2 vr = Elem<DT>::ld(psi, r), vc = Elem<DT>::ld(psi, c);
+    double2 ar = vr, ac = vc;
+#pragma unroll
+    for (int n = 1; n <= 5; n++) {
+        const double2 nr = make_double2(sa * vc.x, sa * vc.y);
+        const double2 nc = make_double2(sb * vr.x, sb * vr.y);
+        vr = nr;
+        vc = nc;
+        ar.x += cf[n] * vr.x;
+        ar.y += cf[n] * vr.y;
+        ac.x += cf[n] * vc.x;
+        ac.y += cf[n] * vc.y;
+    }
+    Elem<DT>::st(psi, r, ar);
+    Elem<DT>::st(psi, c, ac);
+}
+
 // Batched update through the compact pair table of the state's pool: one
-// thread per pair {r, c = r ^ x_k} of the selected generator k, entries +-1.
+// thread per pair of the selected generator.
 template <int DT>
 __global__ void __launch_bounds__(TAYLOR_ROWS_PER_BLOCK)
 k_taylor_compact(const TaylorState *__restrict__ states, const int2 *__restrict__ tasks)
@@ -133,32 +159,76 @@ k_taylor_compact(const TaylorState *__restrict__ states, const int2 *__restrict_
     const PairTable *tb = stp->table;
     const int p0 = gmem(tb->pts)[k * tb->nt], p1 = gmem(tb->pts)[(k + 1) * tb->nt];
     const int p = p0 + task.y * TAYLOR_ROWS_PER_BLOCK + threadIdx.x;
-    if (p >= p1)
+    if (p < p1)
+        taylor_compact_pair<DT>(tb, k, p, *stp->theta, stp->psi);
+}
+
+// Update, norm and rescale of a state of at most NORM_ROWS_PER_BLOCK rows by
+// one workgroup: three launches' work, which for such a state is the launches.
+// The norm is the one block sum of k_norm_partials, in its order.  compact: by
+// the pool's compact pair table.  theta_row (nullable): the state's angle, stored
+// as its angle.
+template <int DT, bool BATCH>
+__global__ void __launch_bounds__(256)
+k_taylor_small(TaylorState single, const TaylorState *__restrict__ states, bool compact, bool renorm,
+               const double *__restrict__ theta_row)
+{
+    const TaylorState *stp = BATCH ? states + blockIdx.x : &single;
+    if (BATCH && VQE_SKIP(*stp))
         return;
-    const uint32_t w = gmem(tb->words)[p];
-    const int64_t r = w & 0x3fffffffu;
-    const int64_t c = r ^ (int64_t)gmem(tb->xmask)[k];
-    const double sa = (w >> 30) & 1u ? -1.0 : 1.0;   // A[r,c]
-    const double sb = (w >> 31) ? -1.0 : 1.0;         // A[c,r]
-    const double theta = *stp->theta;
-    double cf[6];
-    taylor_coeffs(theta, cf);
+    const int tid = threadIdx.x, n = (int)stp->dim;
     void *psi = stp->psi;
-    double2 vr = Elem<DT>::ld(psi, r), vc = Elem<DT>::ld(psi, c);
-    double2 ar = vr, ac = vc;
-#pragma unroll
-    for (int n = 1; n <= 5; n++) {
-        const double2 nr = make_double2(sa * vc.x, sa * vc.y);
-        const double2 nc = make_double2(sb * vr.x, sb * vr.y);
-        vr = nr;
-        vc = nc;
-        ar.x += cf[n] * vr.x;
-        ar.y += cf[n] * vr.y;
-        ac.x += cf[n] * vc.x;
-        ac.y += cf[n] * vc.y;
+    const int32_t kk = stp->k ? *stp->k : 0;
+    double theta = stp->theta_value;
+    if (BATCH) {
+        theta = theta_row ? theta_row[blockIdx.x] : *stp->theta;
+        __syncthreads();      // (every thread has read the angle)
+        if (theta_row && tid == 0)
+            *const_cast<double *>(stp->theta) = theta;
     }
-    Elem<DT>::st(psi, r, ar);
-    Elem<DT>::st(psi, c, ac);
+    if (!stp->k || (kk >= 0 && kk < stp->M)) {
+        if (BATCH && compact) {
+            const PairTable *tb = stp->table;
+            const int p1 = gmem(tb->pts)[(kk + 1) * tb->nt];
+            for (int p = gmem(tb->pts)[kk * tb->nt] + tid; p < p1; p += 256)
+                taylor_compact_pair<DT>(tb, kk, p, theta, psi);
+        } else {
+            const vqe_csr *op = stp->k ? stp->ops + kk : &stp->op;
+            for (int r = tid; r < n; r += 256)
+                taylor_pair_row<DT>(op->rowptr, op->col, op->val, theta, psi, r);
+        }
+    }
+    if (!renorm && !stp->norm2_out)
+        return;
+    __syncthreads();      // the workgroup's updates are read below
+    constexpr int U = NORM_ROWS_PER_BLOCK / 256;
+    double2 p[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        const int r = tid + 256 * u;
+        p[u] = r < n ? Elem<DT>::ld(psi, r) : make_double2(0.0, 0.0);
+    }
+    double s = 0.0;
+#pragma unroll
+    for (int u = 0; u < U; u++)
+        s += p[u].x * p[u].x + p[u].y * p[u].y;
+    __shared__ double red[4];
+    s = wave_sum(s);
+    if ((tid & 63) == 0)
+        red[tid >> 6] = s;
+    __syncthreads();
+    const double n2 = ((red[0] + red[1]) + red[2]) + red[3];
+    if (tid == 0 && stp->norm2_out)
+        stp->norm2_out[0] = n2;
+    if (!renorm)
+        return;
+    const double inv = 1.0 / sqrt(n2);
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        const int r = tid + 256 * u;
+        if (r < n)
+            Elem<DT>::st(psi, r, make_double2(p[u].x * inv, p[u].y * inv));
+    }
 }
 
 template <int DT, bool BATCH>
@@ -376,6 +446,16 @@ void launch_taylor_compact(int dtype, const TaylorState *states, const int2 *tas
         k_taylor_compact<VQE_C64><<<grid, TAYLOR_ROWS_PER_BLOCK, 0, s>>>(states, tasks);
 }
 
+void launch_taylor_small(int dtype, const TaylorState *states, unsigned n_states, bool compact, bool renorm,
+                         const double *theta_row, hipStream_t s)
+{
+    TaylorState dummy{};
+    if (dtype == VQE_C128)
+        k_taylor_small<VQE_C128, true><<<n_states, 256, 0, s>>>(dummy, states, compact, renorm, theta_row);
+    else
+        k_taylor_small<VQE_C64, true><<<n_states, 256, 0, s>>>(dummy, states, compact, renorm, theta_row);
+}
+
 void launch_norm(int dtype, const TaylorState *states, const int2 *tasks, unsigned grid,
                  hipStream_t s)
 {
@@ -414,6 +494,11 @@ static int taylor_single(vqe_ctx *ctx, const vqe_csr *A, double theta, void *psi
     st.norm2_out = norm2_out;
     st.nblocks = (int32_t)nnorm;
     st.renorm = renorm;
+    if (pairing && dim <= NORM_ROWS_PER_BLOCK) {
+        k_taylor_small<DT, false><<<1, 256, 0, s>>>(st, nullptr, false, renorm != 0, nullptr);
+        VQE_LAUNCH_CHECK(ctx);
+        return VQE_OK;
+    }
     if (pairing) {
         const unsigned grid = (unsigned)((dim + TAYLOR_ROWS_PER_BLOCK - 1) / TAYLOR_ROWS_PER_BLOCK);
         k_taylor_pair<DT, false><<<grid, TAYLOR_ROWS_PER_BLOCK, 0, s>>>(st, nullptr, nullptr);
