@@ -152,7 +152,8 @@ def plan_blocked(sched: int, d) -> bool:
 def plan_dict(sched: int, d) -> bool:
     """True when a state's sliced layout keeps most values in a dictionary."""
     from paper_2606_29692_amd import binding as B
-    return bool(sched & B.VQE_SPMV_VDICT) and d.H.dim * d.psi.element_size() <= LDS_STATE_BYTES
+    return bool(sched & B.VQE_SPMV_VDICT) and bool(sched & B.VQE_SPMV_XIDX) and \
+        d.psi.element_size() == 8 and d.H.dim <= 1 << 20
 
 
 def stored_h_bytes(sched: int, ds, entries=None, layout_bytes=None) -> int:
@@ -167,16 +168,19 @@ def stored_h_bytes(sched: int, ds, entries=None, layout_bytes=None) -> int:
     flip-mask indices, 4 bytes per three entries and at most 2 KiB of masks
     per row block in place of the columns.  With the value dictionary, the
     layout's device bytes (``layout_bytes``) without what only its build uses,
-    and 10 KiB of tables per row block."""
+    and 10 KiB of tables per row block (8 KiB per row block and column tile)."""
     from paper_2606_29692_amd import binding as B
     x16, rv = plan_sched_x16(sched, ds), plan_sched_real(sched, ds)
     pad = rv or plan_sched_pad(sched, ds)
     tot = 0
     for i, d in enumerate(ds):
         if plan_dict(sched, d):
-            build = 4 * (5 * 1024 + d.H.dim) + 2 * d.H.dim
-            tot += layout_bytes[i] - build + 10240 * -(-d.H.dim // BLK_ROWS) + \
-                2 * d.H.dim * d.psi.element_size()
+            build, tables = 4 * (5 * 1024 + d.H.dim) + 2 * d.H.dim, 10240 * -(-d.H.dim // BLK_ROWS)
+            if d.H.dim * d.psi.element_size() > LDS_STATE_BYTES:
+                slabs = d.H.dim // SELLT_ROWS * (d.H.dim * d.psi.element_size() // SELLT_TILE_BYTES)
+                build = 26 * 4096 + d.H.dim // 8 + 6 * d.H.dim + 8 * 32 * slabs
+                tables = 8192 * slabs
+            tot += layout_bytes[i] - build + tables + 2 * d.H.dim * d.psi.element_size()
             continue
         if plan_sliced(sched, d):
             big = d.H.dim * d.psi.element_size() > LDS_STATE_BYTES
@@ -705,8 +709,8 @@ def main():
             "h_product_GBps": achieved, "h_product_frac_of_peak": achieved / HBM_PEAK_GBS,
             "traffic_bytes_per_launch": measured_traffic(sched, wl),
             "stored_bytes_per_launch": stored, "stored_GBps": stored / h_s / 1e9,
-            "column_form": (("12-bit codes of (flip mask, magnitude) pairs and the sign, and for "
-                             "the other entries " if dic else "") +
+            "column_form": ((("16-bit" if plan_tiled(ds) else "12-bit") + " codes of (flip mask, "
+                             "magnitude) pairs and the sign, and for the other entries " if dic else "") +
                             ("10-bit flip-mask indices (three per 32-bit word)"
                              if sched & B.VQE_SPMV_XIDX and not plan_tiled(ds) else "16-bit columns") +
                             ", one row per lane in slices of 64 rows sorted by "

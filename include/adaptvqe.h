@@ -665,7 +665,12 @@ VQE_API int64_t vqe_batch_workspace_bytes(const vqe_batch *plan);
  * sorted by their codes, then by their other entries; each lane adds its row's
  * codes in ascending pair order, then the others in column order, so results
  * agree with the other schedules to the rounding of FP64 sums.  Dropped where
- * the index form is and in FP64 storage.
+ * the index form is and in FP64 storage.  A state larger than LDS keeps the
+ * dictionary in the column-tiled sliced product up to 2^20 rows, with a table
+ * of at most 1023 pairs per column tile of the flip masks' 4096 smallest and
+ * 16-bit codes: a block's rows are sorted once for all tiles, and a row adds,
+ * tile by tile ascending, its codes and then its other entries, each in column
+ * order.
  */
 #define VQE_SPMV_VDICT 0x100000
 /*

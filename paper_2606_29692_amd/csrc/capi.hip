@@ -433,7 +433,7 @@ int sliced_build(vqe_ctx *ctx, const vqe_csr *H, int sched, const SellBufs &b, S
         return vqe_fail(ctx, VQE_ENOTSUP, "sliced layout of slot %d: %lld flip masks, more than the "
                         "index form's %d", s, (long long)nx, SPMV_XIDX_MAX);
     const int64_t n = total > 0 ? total : 1;
-    const bool real = (sched & (VQE_SPMV_REAL | VQE_SPMV_RVALS)) != 0;
+    const bool real = (sched & VQE_SPMV_REAL) || (vd && (H->flags & VQE_REAL));
     const int64_t vb = (int64_t)vqe_elem_bytes(H->dtype) / (real ? 2 : 1);
     // 16-bit columns, or one 32-bit word per three entries (whole groups),
     // then the dictionary's codes
@@ -457,6 +457,7 @@ int sliced_build(vqe_ctx *ctx, const vqe_csr *H, int sched, const SellBufs &b, S
     st.sval = *b.val;
     st.srow = (const uint16_t *)m;
     st.sslice = (const int2 *)(m + o_sl);
+    st.rvals = real;
     st.sxtab = xi ? (const uint16_t *)(m + o_xtab) : nullptr;
     st.nx = (int32_t)nx;
     st.dcode = vd ? dcode : nullptr;
@@ -517,6 +518,75 @@ int sliced_tiled_build(vqe_ctx *ctx, const vqe_csr *H, int sched, const SellBufs
     return VQE_OK;
 }
 
+// The same with a dictionary (VQE_SPMV_VDICT): the product's tables in meta,
+// the other entries' codes and then the dictionary's in code, the values in val.
+int vd_tiled_build(vqe_ctx *ctx, const vqe_csr *H, int sched, const SellBufs &b, SpmvState &st, int64_t *entries,
+                   int s)
+{
+    const int64_t dim = H->dim, nb = dim / SPMV_SELLT_ROWS, nt = dim / SPMV_VDT_COLS;
+    const int64_t nlen = nb * nt * SPMV_SLICES_PER_BLOCK;
+    size_t end = 0;
+    auto take = [&](size_t bytes) { size_t o = end; end += vqe_align(bytes); return o; };
+    const size_t o_row = take(dim * 2), o_slice = take(2 * nlen * sizeof(int2)), o_base = take(2 * nb * 8);
+    const size_t o_pair = take(nt * SPMV_VD_PAIRS * sizeof(uint2)), o_mask = take(nb * nt * 4), o_tot = take(24);
+    const size_t o_mark = take(dim / 8), o_xmap = take(dim * 2), o_xtab = take(SPMV_VDT_MASKS * 4);
+    const size_t o_mbase = take(SPMV_VDT_MASKS * 2), o_slots = take(SPMV_VDT_MASKS * (SPMV_VD_VALS + 1) * 4);
+    const size_t o_rl = take(dim * 4), o_len = take(2 * nlen * 4), o_btot = take(2 * nb * 8);
+    int rc = grow_ctx(ctx, b.meta, b.meta_cap, (int64_t)end, "dictionary tables", s);
+    if (rc)
+        return rc;
+    char *m = (char *)*b.meta;
+    VdTiled v{};
+    v.srow = (uint16_t *)(m + o_row);
+    v.slice = (int2 *)(m + o_slice);
+    v.bbase = (int64_t *)(m + o_base);
+    v.pair = (uint2 *)(m + o_pair);
+    v.smask = (uint32_t *)(m + o_mask);
+    v.total = (int64_t *)(m + o_tot);
+    v.mark = (uint32_t *)(m + o_mark);
+    v.xmap = (uint16_t *)(m + o_xmap);
+    v.xtab = (uint32_t *)(m + o_xtab);
+    v.base = (uint16_t *)(m + o_mbase);
+    v.slots = (uint32_t *)(m + o_slots);
+    v.rowlen = (uint32_t *)(m + o_rl);
+    v.len = (int32_t *)(m + o_len);
+    v.btot = (int64_t *)(m + o_btot);
+    launch_vdt_layout(H, v, ctx->stream);
+    VQE_LAUNCH_CHECK(ctx);
+    int64_t *h = ctx->host_scalars;
+    VQE_HIP(ctx, hipMemcpyAsync(h, v.total, 2 * sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
+    VQE_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    const int64_t codes = h[0], other = h[1];
+    if (codes < 0 || other < 0)
+        return vqe_fail(ctx, VQE_EHIP, "dictionary layout of slot %d: bad size", s);
+    const bool real = (H->flags & VQE_REAL) != 0;
+    const int64_t vb = (int64_t)sizeof(float2) / (real ? 2 : 1);
+    const int64_t cb = (int64_t)vqe_align((size_t)(other * 2 + 16));
+    if ((rc = grow_ctx(ctx, b.code, b.code_cap, cb + codes * 2 + 16, "slice codes", s)) ||
+        (rc = grow_ctx(ctx, b.val, b.val_cap, other * vb + 16, "slice values", s)))
+        return rc;
+    uint16_t *dcode = (uint16_t *)((char *)*b.code + cb);
+    launch_vdt_fill(H, v, real, dcode, (uint16_t *)*b.code, *b.val, ctx->stream);
+    VQE_LAUNCH_CHECK(ctx);
+    st.scode = (const uint16_t *)*b.code;
+    st.sval = *b.val;
+    st.srow = v.srow;
+    st.sslice = v.slice + nlen;
+    st.boff = v.bbase + nb;
+    st.dcode = (const uint32_t *)dcode;
+    st.dslice = v.slice;
+    st.dboff = v.bbase;
+    st.rvals = real;
+    st.dpair = v.pair;
+    st.smask = v.smask;
+    st.blk_rows = SPMV_SELLT_ROWS;
+    st.tile_cols = SPMV_VDT_COLS;
+    st.ntiles = (int32_t)nt;
+    st.nblocks = (int32_t)spmv_blocks(dim, sched);
+    *entries = codes + other;
+    return VQE_OK;
+}
+
 // (Re)build slot s's sliced layout (either form) in its plan-owned buffers --
 // tables in prow, codes in col16, values in vre -- and point the slot's host
 // descriptor at it (the caller uploads the descriptor).
@@ -525,8 +595,10 @@ int sliced_fill(vqe_batch *p, int s, const vqe_csr *H, int sched)
     SpmvState &st = reinterpret_cast<SpmvState *>(p->image.data() + p->o_spmv)[s];
     const SellBufs b{&p->prow[s], &p->col16[s], &p->vre[s], &p->prow_cap[s], &p->col16_cap[s],
                      &p->vre_cap[s]};
-    return (sched & VQE_SPMV_BLOCKED) ? sliced_tiled_build(p->ctx, H, sched, b, st, &p->entries[s], s)
-                                      : sliced_build(p->ctx, H, sched, b, st, &p->entries[s], s);
+    auto *build = !(sched & VQE_SPMV_BLOCKED) ? sliced_build
+                  : (sched & VQE_SPMV_VDICT)  ? vd_tiled_build
+                                              : sliced_tiled_build;
+    return build(p->ctx, H, sched, b, st, &p->entries[s], s);
 }
 
 // (Re)build slot s's blocked layout of H (VQE_SPMV_BLOCKED) in its plan-owned
@@ -847,7 +919,9 @@ extern "C" int vqe_batch_create(vqe_ctx *ctx, int32_t B, const vqe_batch_item *i
         const int req = items[s].spmv_schedule ? items[s].spmv_schedule : vqe_default_schedule(H);
         lanes[s] = vqe_batch_schedule(H, req);
         int64_t nblk = spmv_blocks(H->dim, lanes[s]);
-        if (lanes[s] & VQE_SPMV_BLOCKED) {
+        if (lanes[s] & VQE_SPMV_VDICT) {
+            // (parts of blocks, in either form)
+        } else if (lanes[s] & VQE_SPMV_BLOCKED) {
             // the layout lives in the slot's own buffers (blocked_fill,
             // sliced_fill)
             const int64_t rb = (lanes[s] & VQE_SPMV_SLICED) ? SPMV_SELLT_ROWS : SPMV_BLK_ROWS;
@@ -891,14 +965,14 @@ extern "C" int vqe_batch_create(vqe_ctx *ctx, int32_t B, const vqe_batch_item *i
         if (per.empty())
             per.resize(kXcd);
         const int64_t dim = items[s].H->dim;
-        if (lanes[s] & VQE_SPMV_BLOCKED) {
+        if ((lanes[s] & VQE_SPMV_BLOCKED) && !(lanes[s] & VQE_SPMV_VDICT)) {
             const int64_t rb = (lanes[s] & VQE_SPMV_SLICED) ? SPMV_SELLT_ROWS : SPMV_BLK_ROWS;
             const int nb = (int)((dim + rb - 1) / rb);
             for (int b = 0; b < nb; b++)
                 per[p->home(s, b)].push_back(make_int2(s, b));
             continue;
         }
-        if (lanes[s] & VQE_SPMV_TILED) {
+        if ((lanes[s] & VQE_SPMV_TILED) && !(lanes[s] & VQE_SPMV_BLOCKED)) {
             const int nb = (int)((dim + SPMV_LDS_ROWS - 1) / SPMV_LDS_ROWS);
             for (int b = 0; b < nb; b++)
                 for (int t = 0; t < ntiles[s]; t++)
@@ -1223,10 +1297,10 @@ extern "C" int vqe_batch_create(vqe_ctx *ctx, int32_t B, const vqe_batch_item *i
         st.shift = it.H->diag_shift;
         st.nblocks = (int32_t)spmv_blocks(it.H->dim, lanes[s]);
         st.lanes = lanes[s];
-        if (lanes[s] & VQE_SPMV_BLOCKED) {
+        if ((lanes[s] & VQE_SPMV_BLOCKED) && !(lanes[s] & VQE_SPMV_VDICT)) {
             const int64_t rb = (lanes[s] & VQE_SPMV_SLICED) ? SPMV_SELLT_ROWS : SPMV_BLK_ROWS;
             st.nblocks = (int32_t)((it.H->dim + rb - 1) / rb);
-        } else if (lanes[s] & VQE_SPMV_TILED) {
+        } else if ((lanes[s] & VQE_SPMV_TILED) && !(lanes[s] & VQE_SPMV_BLOCKED)) {
             st.tptr = (const int32_t *)(D + o_tptr[s]);
             st.tile_part = (double *)(D + o_tpart[s]);
             st.ntiles = ntiles[s];
@@ -1457,6 +1531,8 @@ int rebind_impl(vqe_batch *p, int32_t slot, const vqe_batch_item *it, const vqe_
         st->dcode = layout->st.dcode;
         st->dslice = layout->st.dslice;
         st->dpair = layout->st.dpair;
+        st->dboff = layout->st.dboff;
+        st->rvals = layout->st.rvals;
         if (sched & VQE_SPMV_BLOCKED) {
             st->boff = layout->st.boff;
             st->smask = layout->st.smask;
@@ -1544,8 +1620,10 @@ extern "C" int vqe_layout_create(vqe_ctx *ctx, const vqe_csr *H, int32_t schedul
     L->dim = H->dim;
     L->H = H;
     const SellBufs b{&L->meta, &L->code, &L->val, &L->meta_cap, &L->code_cap, &L->val_cap};
-    rc = (sched & VQE_SPMV_BLOCKED) ? sliced_tiled_build(ctx, H, sched, b, L->st, &L->entries, -1)
-                                    : sliced_build(ctx, H, sched, b, L->st, &L->entries, -1);
+    auto *build = !(sched & VQE_SPMV_BLOCKED) ? sliced_build
+                  : (sched & VQE_SPMV_VDICT)  ? vd_tiled_build
+                                              : sliced_tiled_build;
+    rc = build(ctx, H, sched, b, L->st, &L->entries, -1);
     if (rc) {
         vqe_layout_destroy(L);
         return rc;

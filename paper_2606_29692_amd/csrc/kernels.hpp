@@ -322,6 +322,24 @@ void launch_vd_layout(const vqe_csr *H, int E, const uint16_t *xmap, const uint1
 void launch_vd_fill(const vqe_csr *H, int E, bool real, const uint16_t *srow, const int2 *sslice,
                     const uint16_t *xmap, const uint16_t *base, const uint2 *pair, uint32_t *code,
                     void *val, uint32_t *dcode, hipStream_t s);
+// the dictionary of a column-tiled state (FP32 storage, 2^15 to 2^20 rows, a
+// multiple of SPMV_SELLT_ROWS): the product's tables srow [dim], slice
+// [2 * nlen] (codes, then other entries; nlen = blocks * tiles * slices), bbase
+// [2 * blocks], pair [tiles * SPMV_VD_PAIRS], smask [blocks * tiles] and total
+// [2] (then the masks' count); the rest is scratch: mark [dim / 32], xmap [dim],
+// xtab and base [SPMV_VDT_MASKS], slots [SPMV_VDT_MASKS * (SPMV_VD_VALS + 1)],
+// rowlen [dim], len [2 * nlen], btot [2 * blocks]
+struct VdTiled {
+    uint16_t *srow, *xmap, *base;
+    uint32_t *smask, *mark, *xtab, *slots, *rowlen;
+    int32_t *len;
+    int2 *slice;
+    int64_t *btot, *bbase, *total;
+    uint2 *pair;
+};
+void launch_vdt_layout(const vqe_csr *H, const VdTiled &v, hipStream_t s);
+void launch_vdt_fill(const vqe_csr *H, const VdTiled &v, bool real, uint16_t *dcode, uint16_t *code, void *val,
+                     hipStream_t s);
 // sliced layout of a column-tiled state (VQE_SPMV_SLICED on a state larger
 // than LDS): per slab of the blocked layout (nt tiles of tc columns) the row
 // order srow [slabs * SPMV_SELLT_ROWS] (first the rows' entry counts), the

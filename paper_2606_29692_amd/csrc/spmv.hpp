@@ -103,6 +103,13 @@ struct SpmvState {
     const uint32_t *dcode;
     const int2 *dslice;
     const uint2 *dpair;
+    // (column-tiled: 16-bit codes, a byte offset into the tile's table of signed
+    // pairs, dslice[(b * ntiles + t) * SPMV_SLICES_PER_BLOCK + k] relative to
+    // dboff[b]; the other entries' sslice likewise, relative to boff[b]; srow per
+    // block; tables dpair[(x >> SPMV_VDT_BITS) * SPMV_VD_PAIRS ...])
+    const int64_t *dboff;
+    // the values beside the dictionary are real parts (H is flagged real)
+    int32_t rvals;
 };
 
 // Column-tiled H product: tile width (state elements staged in LDS per pass)
@@ -134,8 +141,20 @@ struct SpmvState {
 // sorted rows of a block that one workgroup may take alone, with their own
 // partial sums (a quarter of a block)
 #define SPMV_VD_PART_ROWS 512
-// (internal schedule bit) the values beside a dictionary are real parts
-#define VQE_SPMV_RVALS 0x200000
+// column-tiled form: masks, tile width (that of SPMV_SELLT_TILE_BYTES in FP32
+// storage), tiles, codes per lane and load, loads in flight
+#define SPMV_VDT_MASKS 4096
+#define SPMV_VDT_BITS 14
+#define SPMV_VDT_COLS (1 << SPMV_VDT_BITS)
+#define SPMV_VDT_MAX_DIM ((int64_t)1 << 20)
+#define SPMV_VDT_TILES 64
+#define SPMV_VDT_GROUP 4
+#ifndef SPMV_VDT_DEPTH
+#define SPMV_VDT_DEPTH 2
+#endif
+#ifndef SPMV_VDT_ODEPTH
+#define SPMV_VDT_ODEPTH 1
+#endif
 #define SPMV_VD_VALS 4
 #define SPMV_VD_GROUP 10
 #ifndef SPMV_VD_DEPTH
