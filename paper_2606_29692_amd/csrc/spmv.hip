@@ -1072,30 +1072,34 @@ k_sell_fill32(uint32_t *__restrict__ p, int64_t n, uint32_t v)
         p[i] = v;
 }
 
-// Rows of a workgroup of the kernels that read the whole CSR (a wave per row).
+// Rows of a workgroup of the kernels that read the whole CSR (a wave per row,
+// 16 waves).  A row is a chain of dependent reads (bounds, columns, mask
+// numbers), so waves in flight set their time: a 14-qubit H is 256 workgroups,
+// and with four waves each the marks took 34 us, the magnitudes 70 and the
+// rows' counts 26; with sixteen 12, 23 and 10.
 #define SELL_SCAN_ROWS 64
 
 // The masks the operator uses, a bit each in mark [dim / 32 words, at least
 // one] (col and row are below dim = 2^N <= 2^16, so is their XOR); a
 // workgroup's rows gather in LDS first.
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(1024)
 k_sell_xmark(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col, int64_t dim,
              uint32_t *__restrict__ mark)
 {
     __shared__ uint32_t s_mark[SPMV_X16_MAX_DIM / 32];
     const int tid = threadIdx.x, lane = tid & 63, words = (int)((dim + 31) / 32);
-    for (int i = tid; i < words; i += 256)
+    for (int i = tid; i < words; i += 1024)
         s_mark[i] = 0u;
     __syncthreads();
     const int64_t r0 = (int64_t)blockIdx.x * SELL_SCAN_ROWS;
-    for (int64_t r = r0 + (tid >> 6); r < r0 + SELL_SCAN_ROWS && r < dim; r += 4)
+    for (int64_t r = r0 + (tid >> 6); r < r0 + SELL_SCAN_ROWS && r < dim; r += 16)
         for (int k = rowptr[r] + lane; k < rowptr[r + 1]; k += VQE_WAVE) {
             const uint32_t x = (uint32_t)col[k] ^ (uint32_t)r;
             if (!(s_mark[x >> 5] >> (x & 31u) & 1u))
                 atomicOr(&s_mark[x >> 5], 1u << (x & 31u));
         }
     __syncthreads();
-    for (int i = tid; i < words; i += 256)
+    for (int i = tid; i < words; i += 1024)
         if (s_mark[i])
             atomicOr(&mark[i], s_mark[i]);
 }
@@ -1165,7 +1169,7 @@ __device__ __forceinline__ void vd_insert(uint32_t *slots, uint32_t *bad, int i,
     bad[i] = 1u;
 }
 
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(1024)
 k_vd_collect(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
              const float2 *__restrict__ val, int64_t dim, const uint16_t *__restrict__ xmap,
              uint32_t *__restrict__ slots, uint32_t *__restrict__ bad)
@@ -1173,13 +1177,13 @@ k_vd_collect(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col
     __shared__ uint32_t s_slots[SPMV_XIDX_MAX * SPMV_VD_VALS];
     __shared__ uint32_t s_bad[SPMV_XIDX_MAX];
     const int tid = threadIdx.x, lane = tid & 63;
-    for (int i = tid; i < SPMV_XIDX_MAX * SPMV_VD_VALS; i += 256)
+    for (int i = tid; i < SPMV_XIDX_MAX * SPMV_VD_VALS; i += 1024)
         s_slots[i] = SPMV_VD_EMPTY;
-    for (int i = tid; i < SPMV_XIDX_MAX; i += 256)
+    for (int i = tid; i < SPMV_XIDX_MAX; i += 1024)
         s_bad[i] = 0u;
     __syncthreads();
     const int64_t r0 = (int64_t)blockIdx.x * SELL_SCAN_ROWS;
-    for (int64_t r = r0 + (tid >> 6); r < r0 + SELL_SCAN_ROWS && r < dim; r += 4)
+    for (int64_t r = r0 + (tid >> 6); r < r0 + SELL_SCAN_ROWS && r < dim; r += 16)
         for (int k = rowptr[r] + lane; k < rowptr[r + 1]; k += VQE_WAVE) {
             const int i = xmap[(uint32_t)col[k] ^ (uint32_t)r];
             const float2 v = val[k];
@@ -1191,7 +1195,7 @@ k_vd_collect(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col
                 vd_insert(s_slots, s_bad, i, __float_as_uint(v.x) & 0x7fffffffu);
         }
     __syncthreads();
-    for (int i = tid; i < SPMV_XIDX_MAX; i += 256) {
+    for (int i = tid; i < SPMV_XIDX_MAX; i += 1024) {
         if (s_bad[i]) {
             bad[i] = 1u;
             continue;
@@ -1257,14 +1261,14 @@ k_vd_number(const uint32_t *__restrict__ slots, const uint32_t *__restrict__ bad
 
 // Entries of each row in the dictionary (low half) and beside it (high half).
 template <int MASKS>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(1024)
 k_vd_rows(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col, int64_t dim,
           const uint16_t *__restrict__ xmap, const uint16_t *__restrict__ base,
           uint32_t *__restrict__ len)
 {
     const int tid = threadIdx.x, lane = tid & 63;
     const int64_t r0 = (int64_t)blockIdx.x * SELL_SCAN_ROWS;
-    for (int64_t r = r0 + (tid >> 6); r < r0 + SELL_SCAN_ROWS && r < dim; r += 4) {
+    for (int64_t r = r0 + (tid >> 6); r < r0 + SELL_SCAN_ROWS && r < dim; r += 16) {
         const int k0 = rowptr[r], k1 = rowptr[r + 1];
         int n = 0;
         for (int k = k0; k < k1; k += VQE_WAVE) {
@@ -3273,7 +3277,7 @@ k_spmv_sellt(const SpmvState *__restrict__ states, const int2 *__restrict__ task
 // its longest row, codes to groups of four, other entries to pairs (18 qubits:
 // 1.33 times the entries).  About 3 instead of 10 bytes per entry: two 18-qubit
 // states 431 us, bound by HBM -> 217 us, sixteen of 16 qubits 525 -> 230,
-// one of 20 qubits 1388 -> 736; bound now by the two LDS gathers of a code (30
+// one of 20 qubits 1388 -> 736; bound now by the two LDS gathers of a code (26
 // clocks per CU for 64 codes; about 22 where the state fits LDS) and each tile's
 // staging and barriers.  Loads in flight: with two groups of codes and one of
 // the others no register spills (three groups of codes 233 us, one 260).
@@ -3930,7 +3934,7 @@ void launch_sell_xtab(const vqe_csr *H, uint32_t *mark, uint16_t *xmap, uint16_t
 {
     const unsigned g = (unsigned)((H->dim + SELL_SCAN_ROWS - 1) / SELL_SCAN_ROWS);
     fill32(mark, (H->dim + 31) / 32, 0u, s);
-    k_sell_xmark<<<g, 256, 0, s>>>(H->rowptr, H->col, H->dim, mark);
+    k_sell_xmark<<<g, 1024, 0, s>>>(H->rowptr, H->col, H->dim, mark);
     k_sell_xscan<<<1, 1024, 0, s>>>(mark, H->dim, xmap, xtab, nx);
 }
 
@@ -3943,9 +3947,9 @@ void launch_vd_layout(const vqe_csr *H, int E, const uint16_t *xmap, const uint1
     uint32_t *slots = scratch, *bad = slots + SPMV_XIDX_MAX * SPMV_VD_VALS, *len = bad + SPMV_XIDX_MAX;
     fill32(slots, SPMV_XIDX_MAX * SPMV_VD_VALS, SPMV_VD_EMPTY, s);
     fill32(bad, SPMV_XIDX_MAX, 0u, s);
-    k_vd_collect<<<g, 256, 0, s>>>(H->rowptr, H->col, (const float2 *)H->val, H->dim, xmap, slots, bad);
+    k_vd_collect<<<g, 1024, 0, s>>>(H->rowptr, H->col, (const float2 *)H->val, H->dim, xmap, slots, bad);
     k_vd_number<<<1, 1024, 0, s>>>(slots, bad, xtab, nx, pair, base);
-    k_vd_rows<SPMV_XIDX_MAX><<<g, 256, 0, s>>>(H->rowptr, H->col, H->dim, xmap, base, len);
+    k_vd_rows<SPMV_XIDX_MAX><<<g, 1024, 0, s>>>(H->rowptr, H->col, H->dim, xmap, base, len);
     k_vd_sort<<<(unsigned)nb, 1024, 0, s>>>(len, H->dim, E, srow, slen, ns);
     k_sell_scan<<<2, VQE_WAVE, 0, s>>>(slen, ns, sslice, total);
 }
@@ -4007,7 +4011,7 @@ void launch_vdt_layout(const vqe_csr *H, const VdTiled &v, hipStream_t s)
     (void)hipFuncSetAttribute((const void *)k_vdt_collect, hipFuncAttributeMaxDynamicSharedMemorySize, (int)set_lds);
     k_vdt_collect<<<g, 1024, set_lds, s>>>(H->rowptr, H->col, (const float2 *)H->val, dim, rows, v.xmap, slots, bad);
     k_vdt_number<<<1, 1024, 0, s>>>(slots, bad, v.xtab, v.total + 2, v.pair, v.base);
-    k_vd_rows<SPMV_VDT_MASKS><<<gs, 256, 0, s>>>(H->rowptr, H->col, dim, v.xmap, v.base, v.rowlen);
+    k_vd_rows<SPMV_VDT_MASKS><<<gs, 1024, 0, s>>>(H->rowptr, H->col, dim, v.xmap, v.base, v.rowlen);
     k_vd_sort<<<(unsigned)nb, 1024, 0, s>>>(v.rowlen, dim, 2, v.srow, v.len, nb * SPMV_SLICES_PER_BLOCK);
     k_vdt_count<<<(unsigned)(nb * SPMV_SLICES_PER_BLOCK), 256, 0, s>>>(H->rowptr, H->col, dim, (int32_t)nt, v.srow,
                                                                       v.xmap, v.base, v.len, nlen, v.smask);
