@@ -487,7 +487,7 @@ VQE_API int vqe_batch_layout_entries(const vqe_batch *plan, int32_t slot, int64_
  * s = theta - theta^3/6 + theta^5/120 and c = theta^2/2 - theta^4/24, so the
  * energy is a ratio of quadratic forms in (1, s, c) built from psi, A psi,
  * A^2 psi and two more H products per state; it is minimised in FP64 over a
- * 256-point grid and refined by golden-section search.  The chosen angle is
+ * 256-point grid and refined by sections of 64 points.  The chosen angle is
  * written to the plan's theta before the update.  Allocates the plan's
  * line-search workspace (4 vectors per state) on first use; theta_max = 0
  * disables.  Errors: VQE_EINVAL (bad theta_max), VQE_ENOTSUP (a generator of
@@ -506,7 +506,7 @@ VQE_API int vqe_batch_set_line_search(vqe_batch *plan, double theta_max);
  * before update m and R the later updates, the ansatz is
  * R L + s(t) R A L + c(t) R A^2 L, so each visit costs three H products and
  * the later updates applied to three vectors; the energy ratio is minimised
- * in FP64 (256-point grid, golden-section refinement; the current angle is
+ * in FP64 (256-point grid, refined by 64-point sections; the current angle is
  * kept unless something is lower).
  *   ks      DEVICE int32 [B * ld]: row s holds slot s's generator indices
  *           (indices outside [0, M) leave that update out)
