@@ -1345,6 +1345,15 @@ __device__ __forceinline__ uint32_t vd_word(uint32_t a, uint32_t b, uint32_t e)
 {
     return a << 3 | b << 15 | e << 27 | e >> 5;
 }
+// The wave's accesses to LDS before this come before those after it.  A wave's
+// LDS operations complete in order, so it only binds the compiler, which may
+// otherwise take a lane's own last write for what another lane has overwritten.
+__device__ __forceinline__ void wave_lds_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 __device__ __forceinline__ uint32_t vd_byte(uint32_t w) { return __builtin_amdgcn_alignbit(w, w, 27) & 0xffu; }
 
 // Both streams of one slice per workgroup, a row per wave in turn.  A row's
@@ -1394,12 +1403,14 @@ k_vd_fill(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
         };
         if (lane < SPMV_VD_PAIRS / 32)
             bits[lane] = 0u;
+        wave_lds_order();
         for (int k = k0 + lane; k < k1; k += VQE_WAVE) {
             int m;
             const int p = pair_of(k, m);
             if (p >= 0)
                 atomicOr(&bits[p >> 5], 1u << (p & 31));
         }
+        wave_lds_order();
         int inc = lane < SPMV_VD_PAIRS / 32 ? __popc(bits[lane]) : 0;
         const int own = inc;
 #pragma unroll
@@ -1410,6 +1421,7 @@ k_vd_fill(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
         }
         if (lane < SPMV_VD_PAIRS / 32)
             pre[lane] = (uint16_t)(inc - own);
+        wave_lds_order();
         const int nd = __shfl(inc, VQE_WAVE - 1, VQE_WAVE);
         auto eat = [&](int j) { return (int64_t)se.x + ((int64_t)(j / E) * VQE_WAVE + lr) * E + j % E; };
         int ne = 0;
@@ -1433,6 +1445,7 @@ k_vd_fill(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
             }
             ne += __popcll(eb);
         }
+        wave_lds_order();
         auto code_at = [&](int j) { return j < nd ? (uint32_t)buf[j] : 2u * (SPMV_VD_PAIRS - 1); };
         for (int w = lane; w < sd.y / SPMV_VD_GROUP * 4; w += VQE_WAVE) {
             const int g = w >> 2, q = w & 3, j = g * SPMV_VD_GROUP;
@@ -1445,6 +1458,7 @@ k_vd_fill(const int32_t *__restrict__ rowptr, const int32_t *__restrict__ col,
         auto idx_at = [&](int j) { return j < ne ? (uint32_t)buf[nd + j] : 0u; };
         for (int w = lane; w < se.y / 3; w += VQE_WAVE)
             code[eat(3 * w) / 3] = idx_at(3 * w) | idx_at(3 * w + 1) << 10 | idx_at(3 * w + 2) << 20;
+        wave_lds_order();      // the next row takes the buffers
     }
 }
 

@@ -188,3 +188,44 @@ def test_vdict_fp64_storage_takes_the_index_form(ctx):
     b = _products(ctx, H, pool, [psi], (3 | VD) & ~B.VQE_SPMV_VDICT)
     assert torch.equal(torch.view_as_real(a[0][0]), torch.view_as_real(b[0][0]))
     assert torch.equal(a[1], b[1])
+
+
+def _ragged(n, seed):
+    """Rows of 0 to 150 entries in no order, some with codes only, some with none:
+    the masks' magnitudes are one, two or (past four) per row and mask their own."""
+    rng = np.random.default_rng(seed)
+    dim = 1 << n
+    xs = rng.choice(dim, size=150, replace=False)
+    kinds = rng.integers(0, 3, xs.size)
+    rowptr, cols, vals = [0], [], []
+    for r in range(dim):
+        k = rng.choice(xs.size, size=rng.choice([0, 1, 7, 63, 64, 65, 128, 150]), replace=False)
+        c = xs[k] ^ r
+        v = np.where(kinds[k] == 0, 0.5 + k, np.where(kinds[k] == 1, rng.choice([0.25, 2.0], k.size),
+                                                      rng.uniform(0.1, 1.0, k.size)))
+        v = v * rng.choice([-1.0, 1.0], k.size)
+        at = np.argsort(c)
+        cols.append(c[at])
+        vals.append(v[at])
+        rowptr.append(rowptr[-1] + k.size)
+    rowptr = torch.from_numpy(np.array(rowptr, dtype=np.int32)).cuda()
+    col = torch.from_numpy(np.concatenate(cols).astype(np.int32)).cuda()
+    val = torch.from_numpy(np.concatenate(vals).astype(np.complex64)).cuda()
+    desc = B.vqe_csr()
+    desc.n_qubits, desc.dim, desc.nnz, desc.dtype, desc.flags = n, dim, col.numel(), B.VQE_C64, B.VQE_REAL
+    desc.rowptr, desc.col, desc.val = rowptr.data_ptr(), col.data_ptr(), val.data_ptr()
+    return B.DeviceCSR(desc, rowptr, col, val)
+
+
+@pytest.mark.parametrize("n", [8, 11])
+def test_vdict_rows_one_after_another(ctx, n):
+    """The builder's wave takes rows in turn through the same buffers: long ones
+    behind short and empty ones, and rows that leave some lanes without an entry."""
+    H = _ragged(n, n)
+    with torch.cuda.stream(ctx.stream):
+        pool = B.MatrixFreePool(_pool(n), "c64")
+    for sched in (3 | VD, 6 | VD | B.VQE_SPMV_REAL):
+        print(f"vdict ragged n={n} schedule {sched:#x}", flush=True)
+        psi = _state(n, "complex", 6)
+        (sigma,), _ = _products(ctx, H, pool, [psi], sched)
+        _check(H, psi, sigma)
