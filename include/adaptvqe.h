@@ -648,10 +648,11 @@ VQE_API int64_t vqe_batch_workspace_bytes(const vqe_batch *plan);
  * in LDS beside the state) instead of the 16-bit column: three 10-bit indices
  * to a 32-bit word (E / 3 words per group), 1.33 bytes per entry instead of 2.  Pads take index 0
  * and the value zero.  The plan (or vqe_layout_create) reports VQE_ENOTSUP
- * for an operator with more than 1024 distinct flip masks; a state larger
- * than LDS runs the column-tiled sliced product with E = 2.  Each lane adds
- * its row's entries in the order of the 16-bit column form, so the results
- * equal that form's bit for bit (the pads add zeros).
+ * for an operator with more than 1024 distinct flip masks, unless the schedule
+ * has VQE_SPMV_VDICT below; a state larger than LDS runs the column-tiled
+ * sliced product with E = 2.  Each lane adds its row's entries in the order of
+ * the 16-bit column form, so the results equal that form's bit for bit (the
+ * pads add zeros).
  */
 #define VQE_SPMV_XIDX 0x80000
 /*
@@ -661,16 +662,20 @@ VQE_API int64_t vqe_batch_workspace_bytes(const vqe_batch *plan);
  * codes, the number of a (mask, magnitude) pair and a sign, beside a
  * per-operator table of at most 1023 pairs (masks past that, and all others,
  * keep the index form, as real parts for an operator flagged VQE_REAL).  The
- * values are the CSR's, bit for bit.  Rows are
- * sorted by their codes, then by their other entries; each lane adds its row's
- * codes in ascending pair order, then the others in column order, so results
- * agree with the other schedules to the rounding of FP64 sums.  Dropped where
- * the index form is and in FP64 storage.  A state larger than LDS keeps the
- * dictionary in the column-tiled sliced product up to 2^20 rows, with a table
- * of at most 1023 pairs per column tile of the flip masks' 4096 smallest and
- * 16-bit codes: a block's rows are sorted once for all tiles, and a row adds,
- * tile by tile ascending, its codes and then its other entries, each in column
- * order.
+ * values are the CSR's, bit for bit.  Rows are sorted by their codes, then by
+ * their other entries; each lane adds its row's codes in ascending pair order,
+ * then the others in column order, so results agree with the other schedules
+ * to the rounding of FP64 sums.  An operator with more than 1024 distinct flip
+ * masks has all its entries as 16-bit columns (real parts where it is flagged
+ * VQE_REAL), each row summed in column order.  A pad multiplies the row's own
+ * amplitude by zero (column-tiled, another amplitude of the state), so an
+ * infinite or NaN amplitude may turn up in rows that have no entry of its
+ * column.  Dropped where the index form is and in FP64 storage.
+ * A state larger than LDS keeps the dictionary in the column-tiled sliced
+ * product up to 2^20 rows, with a table of at most 1023 pairs per column tile
+ * of the flip masks' 4096 smallest and 16-bit codes: a block's rows are sorted
+ * once for all tiles, and a row adds, tile by tile ascending, its codes and
+ * then its other entries, each in column order.
  */
 #define VQE_SPMV_VDICT 0x100000
 /*

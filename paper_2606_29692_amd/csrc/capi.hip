@@ -390,8 +390,8 @@ int codes_fill(vqe_batch *p, int s, const vqe_csr *H, int sched)
 int sliced_build(vqe_ctx *ctx, const vqe_csr *H, int sched, const SellBufs &b, SpmvState &st,
                  int64_t *entries, int s)
 {
-    const int E = sched & 0xff;
-    const bool xi = (sched & VQE_SPMV_XIDX) != 0, vd = (sched & VQE_SPMV_VDICT) != 0;
+    int E = sched & 0xff;
+    bool xi = (sched & VQE_SPMV_XIDX) != 0, vd = (sched & VQE_SPMV_VDICT) != 0;
     const int64_t nb = (H->dim + SPMV_LDS_ROWS - 1) / SPMV_LDS_ROWS;
     const int64_t ns = nb * SPMV_SLICES_PER_BLOCK, streams = vd ? 2 : 1;
     const size_t o_len = vqe_align((size_t)H->dim * sizeof(uint16_t));
@@ -426,14 +426,26 @@ int sliced_build(vqe_ctx *ctx, const vqe_csr *H, int sched, const SellBufs &b, S
     int64_t *h = ctx->host_scalars;     // the totals and the masks' count
     VQE_HIP(ctx, hipMemcpyAsync(h, tot, 3 * sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
     VQE_HIP(ctx, hipStreamSynchronize(ctx->stream));
-    const int64_t total = h[0], codes = vd ? h[1] : 0, nx = xi ? h[2] : 0;
+    int64_t nx = xi ? h[2] : 0;
+    const bool real = (sched & VQE_SPMV_REAL) || (vd && (H->flags & VQE_REAL));
+    // a dictionary schedule takes any operator: one with more masks than the
+    // index form holds has its entries as 16-bit columns
+    if (vd && nx > SPMV_XIDX_MAX) {
+        xi = vd = false;
+        nx = 0;
+        E = SPMV_VD_COLS(real);
+        launch_sell_layout(H, E, (uint16_t *)m, (int32_t *)(m + o_len), (int2 *)(m + o_sl), tot, ctx->stream);
+        VQE_LAUNCH_CHECK(ctx);
+        VQE_HIP(ctx, hipMemcpyAsync(h, tot, sizeof(int64_t), hipMemcpyDeviceToHost, ctx->stream));
+        VQE_HIP(ctx, hipStreamSynchronize(ctx->stream));
+    }
+    const int64_t total = h[0], codes = vd ? h[1] : 0;
     if (total < 0 || total > 0x7fffffffLL || codes < 0 || codes > 0x7fffffffLL)
         return vqe_fail(ctx, VQE_ESIZE, "sliced layout of slot %d: %lld entries", s, (long long)(total + codes));
     if (nx < 0 || nx > SPMV_XIDX_MAX)
         return vqe_fail(ctx, VQE_ENOTSUP, "sliced layout of slot %d: %lld flip masks, more than the "
                         "index form's %d", s, (long long)nx, SPMV_XIDX_MAX);
     const int64_t n = total > 0 ? total : 1;
-    const bool real = (sched & VQE_SPMV_REAL) || (vd && (H->flags & VQE_REAL));
     const int64_t vb = (int64_t)vqe_elem_bytes(H->dtype) / (real ? 2 : 1);
     // 16-bit columns, or one 32-bit word per three entries (whole groups),
     // then the dictionary's codes

@@ -2029,17 +2029,18 @@ __device__ __forceinline__ void sell_block(const SpmvState &st, const int2 t)
             kb = SPMV_SLICES_PER_BLOCK;
         }
     }
+    static_assert(!VD || DT == VQE_C64, "the dictionary form: FP32 storage");
+    constexpr bool DICT = VD && XI;     // (VD alone: an operator past the index form)
     SellWave<DT, E, D, RV, XI> w;
     w.init(st, blk, lane, ka, kb);
     if constexpr (XI) {
         static_assert(SPMV_XIDX_MAX <= 1024, "one mask per thread");
         s_xt[tid] = tid < st.nx ? gmem(st.sxtab)[tid] : (uint16_t)0;
     }
-    // VD: the dictionary's codes run first, then the other entries, whose first
+    // DICT: the dictionary's codes run first, then the other entries, whose first
     // groups load meanwhile
-    static_assert(!VD || (XI && DT == VQE_C64), "the dictionary form: FP32 storage, with the index form");
     DictWave<SPMV_VD_DEPTH> dw;
-    if constexpr (VD) {
+    if constexpr (DICT) {
         const sell_v2u pr = gmem(reinterpret_cast<const sell_v2u *>(st.dpair))[tid];
         s_pair[2 * tid] = make_uint2(pr.x, pr.y);
         s_pair[2 * tid + 1] = make_uint2(pr.x ^ 0x80000000u, pr.y);
@@ -2047,7 +2048,7 @@ __device__ __forceinline__ void sell_block(const SpmvState &st, const int2 t)
     }
     double2 sa, sb;
     auto products = [&](const auto *s_x) {
-        if constexpr (VD) {
+        if constexpr (DICT) {
             double2 da, db;
             if (w.ng > 0)
                 w.prefetch();
@@ -2067,7 +2068,7 @@ __device__ __forceinline__ void sell_block(const SpmvState &st, const int2 t)
             sell_finish(st, blk, w, s_x, s_sig, sa, sb);
     };
     auto first_groups = [&]() {
-        if constexpr (VD) {
+        if constexpr (DICT) {
             if (dw.ng > 0)
                 dw.prefetch();
         } else if (w.ng > 0) {
@@ -2128,11 +2129,25 @@ k_spmv_sell(const SpmvState *__restrict__ states, const int2 *__restrict__ tasks
     const SpmvState st = states[t.x];
     if (VQE_SKIP(st))
         return;
-    // beside a dictionary the operator says whether its values are real parts
-    if constexpr (VD && !RV) {
-        if (st.rvals) {
-            sell_block<DT, E, D, true, XI, VD, RS>(st, t);
+    // beside a dictionary the operator says whether its values are real parts;
+    // past the index form (no codes) its entries are 16-bit columns, four a
+    // group of real parts, two of complex values
+    if constexpr (VD) {
+        if (!st.dcode) {
+            if constexpr (!RV) {
+                if (!st.rvals) {
+                    sell_block<DT, SPMV_VD_COLS(false), 4, false, false, true, RS>(st, t);
+                    return;
+                }
+            }
+            sell_block<DT, SPMV_VD_COLS(true), 3, true, false, true, RS>(st, t);
             return;
+        }
+        if constexpr (!RV) {
+            if (st.rvals) {
+                sell_block<DT, E, D, true, XI, VD, RS>(st, t);
+                return;
+            }
         }
     }
     sell_block<DT, E, D, RV, XI, VD, RS>(st, t);

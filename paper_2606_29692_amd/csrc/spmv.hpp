@@ -99,7 +99,8 @@ struct SpmvState {
     // codes 2q and 2q + 1 of the ten in word q, the ninth spread over words 0
     // and 1, the tenth over 2 and 3 (vd_word); a code is twice the pair's
     // number, plus one for a negative value (pads: the last pair, which is
-    // zero).  scode, sval and sslice then hold the other entries
+    // zero).  scode, sval and sslice then hold the other entries.  dcode null:
+    // more masks than the index form takes, every entry a 16-bit column
     const uint32_t *dcode;
     const int2 *dslice;
     const uint2 *dpair;
@@ -156,6 +157,8 @@ struct SpmvState {
 #define SPMV_VDT_ODEPTH 1
 #endif
 #define SPMV_VD_VALS 4
+// entries per group of an operator with more masks than the index form takes
+#define SPMV_VD_COLS(real) ((real) ? 4 : 2)
 #define SPMV_VD_GROUP 10
 #ifndef SPMV_VD_DEPTH
 #define SPMV_VD_DEPTH 3

@@ -15,6 +15,7 @@ torch = pytest.importorskip("torch")
 import paper_2606_29692_amd as P  # noqa: E402
 from paper_2606_29692_amd import batch as PB  # noqa: E402
 from paper_2606_29692_amd import binding as B  # noqa: E402
+from paper_2606_29692_amd import tune as T  # noqa: E402
 
 VD = B.VQE_SPMV_LDS | B.VQE_SPMV_SLICED | B.VQE_SPMV_XIDX | B.VQE_SPMV_VDICT
 SCHEDULES = [3 | VD, 6 | VD, 3 | VD | B.VQE_SPMV_REAL, 6 | VD | B.VQE_SPMV_REAL]
@@ -229,3 +230,50 @@ def test_vdict_rows_one_after_another(ctx, n):
         psi = _state(n, "complex", 6)
         (sigma,), _ = _products(ctx, H, pool, [psi], sched)
         _check(H, psi, sigma)
+
+
+@pytest.mark.parametrize("form", ["any", "complex"])
+def test_vdict_more_masks_than_the_index_form(ctx, form):
+    """The shipped 12-qubit schedules take operators of more than 1024 flip masks
+    (entries as 16-bit columns): real and complex ones, alone and in batches of whole,
+    halved and quartered blocks, through plans, layouts and rebinding to and from
+    an operator with a dictionary."""
+    n = 12
+    cu, _ = ctx.info()
+    with torch.cuda.stream(ctx.stream):
+        pool = B.MatrixFreePool(_pool(n), "c64")
+        ops = {"few": _sum(n, 300, lambda i: 1 + i % 5, True, 21), "1100": _sum(n, 1100, lambda i: 1, True, 22),
+               "1500": _sum(n, 1500, lambda i: 1 + i % 6, True, 23), "1100c": _sum(n, 1100, lambda i: 1, False, 24)}
+        ops = {k: B.csr_build_from_pauli(ctx, *v, dtype="c64") for k, v in ops.items()}
+        psi = {k: _state(n, k, 7) for k in ("real", "complex")}
+
+    class Shape:
+        n_qubits, dtype, key = n, "c64", (n, 4, "jw")
+    sched = T.schedule_for(ctx, Shape, value_form=form)
+    for name, H in ops.items():
+        for kind in psi:
+            ref = None
+            for count in (1, cu // 4 + 1, cu // 2 + 1):
+                print(f"vdict masks {form} {name} {kind} x{count}", flush=True)
+                sigma, energy = _products(ctx, H, pool, [psi[kind].clone() for _ in range(count)], sched)
+                if ref is None:
+                    ref = sigma[0], energy[0]
+                    _check(H, psi[kind], sigma[0])
+                assert torch.equal(torch.view_as_real(sigma[-1]), torch.view_as_real(ref[0]))
+                assert torch.equal(energy, ref[1].expand_as(energy))
+    # a slot of the real schedule takes real operators only, as before
+    names = ["few", "1100", "few", "1500"] + (["1100c", "few"] if form == "complex" else [])
+    with torch.cuda.stream(ctx.stream):
+        plan = B.BatchPlan(ctx, [(ops["few"], pool, psi["complex"])], schedules=[sched])
+        for name in names:
+            H = ops[name]
+            layout = B.Layout(ctx, H, sched)
+            alone = _products(ctx, H, pool, [psi["complex"]], sched)[0][0]
+            for lay in (layout, None):
+                print(f"vdict masks rebind {form} {name} layout={lay is not None}", flush=True)
+                plan.rebind(0, H, pool, psi["complex"], layout=lay)
+                plan.step(update=False, graph=True)
+                ctx.stream.synchronize()
+                assert torch.equal(torch.view_as_real(plan.sigma[0]), torch.view_as_real(alone))
+            layout.close()
+        plan.close()
