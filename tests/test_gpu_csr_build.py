@@ -3,6 +3,8 @@ wave, one and many waves per 64 rows, groups beyond the 64-row kernels' table,
 registers beyond its dense prefix table, operators passed as a kernel argument,
 through pinned staging and from pageable memory; every entry bit for bit the
 oracle's ordered sum."""
+import time
+
 import numpy as np
 import pytest
 
@@ -78,3 +80,48 @@ def test_csr_build_shift_keeps_the_diagonal(ctx, n, identity):
     sign = 1.0 - 2.0 * (np.bitwise_count(o.col[diag].astype(np.uint64) & np.uint64(5)) % 2)
     want[diag] = (0.75 * sign if identity else 0.0) - 0.5
     np.testing.assert_array_equal(d.val.cpu().numpy(), want.astype(np.complex64))
+
+
+@pytest.mark.parametrize("n,T,masks", [(9, 511, 200), (9, 512, 200), (12, 30000, 4096), (16, 20000, 1900), (23, 600, 2)])
+def test_csr_build_term_order(ctx, n, T, masks):
+    """Terms given in any order compile as the same terms grouped by flip mask
+    beforehand (each group's in the given order), on both sides of the sizes where
+    the grouping changes."""
+    print(f"csr build order n={n} T={T} masks={masks}", flush=True)
+    rng = np.random.default_rng(n)
+    x = rng.choice(rng.choice(1 << n, size=masks, replace=False).astype(np.uint64), size=T)
+    z = rng.integers(0, 1 << n, T).astype(np.uint64)
+    c = rng.standard_normal(T) + 1j * rng.standard_normal(T)
+    at = np.argsort(x, kind="stable")
+    if masks > 2048:      # (rows of at most 2048 entries)
+        c[x >= np.uint64(2000)] = 0
+    a = B.csr_build_from_pauli(ctx, n, x, z, c)
+    b = B.csr_build_from_pauli(ctx, n, x[at], z[at], c[at])
+    torch.cuda.synchronize()
+    assert a.nnz == b.nnz
+    assert torch.equal(a.rowptr, b.rowptr) and torch.equal(a.col, b.col)
+    assert torch.equal(torch.view_as_real(a.val).view(torch.int64), torch.view_as_real(b.val).view(torch.int64))
+
+
+def test_csr_build_of_many_terms_costs_no_more_out_of_order(ctx):
+    """Grouping 10^5 terms is a small part of compiling them: given out of order
+    they took three times as long as grouped when they were sorted by comparison."""
+    rng = np.random.default_rng(1)
+    n, T = 8, 100000
+    x = rng.integers(0, 1 << n, T).astype(np.uint64)
+    z = rng.integers(0, 1 << n, T).astype(np.uint64)
+    c = rng.standard_normal(T) + 0j
+    at = np.argsort(x, kind="stable")
+
+    def best(*terms):
+        times = []
+        for _ in range(7):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            B.csr_build_from_pauli(ctx, n, *terms)
+            torch.cuda.synchronize()
+            times.append(time.perf_counter() - t)
+        return min(times)
+    mixed, grouped = best(x, z, c), best(x[at], z[at], c[at])
+    print(f"csr build of {T} terms: out of order {mixed * 1e3:.2f} ms, grouped {grouped * 1e3:.2f} ms", flush=True)
+    assert mixed <= 2 * grouped
