@@ -255,8 +255,8 @@ k_row_fill(int64_t dim, OpInline inl, const unsigned char *__restrict__ mem, OpL
 
 // The same two phases with one wave per row, its groups over the lanes, and a
 // bitonic sort of the kept entries in LDS: registers of more than kMaxDense
-// qubits (no dense table over x >> 6) and operators of more than kMaxGroups
-// groups.
+// qubits (no dense table over x >> 6), operators of more than kMaxGroups
+// groups, and few rows of many terms.
 template <bool REAL>
 __global__ void __launch_bounds__(64)
 k_wave_count(int64_t dim, const unsigned char *__restrict__ mem, OpLayout L, double tol,
@@ -671,7 +671,16 @@ try {
     int64_t G = 0;
     for (int64_t i = 0; i < T; i++)
         G += i == 0 || term_x(i) != term_x(i - 1);
-    const bool wide = n_qubits <= kMaxDense && G <= kMaxGroups;   // the 64-row kernels
+    // the 64-row kernels, unless few rows have many terms: 2^11 rows are 32 of
+    // their workgroups, whose waves take a group's terms one after another, where
+    // one wave per row has 32 times the waves and a group per lane (sizing and
+    // fill, 8 qubits: 64 groups of 8 terms 71 us either way, of 200 742 against 386;
+    // 11 qubits: 256 of 8 157 and 150, of 200 2004 and 1464; from 2^12 rows on the
+    // 64-row kernels are the faster, or near).  Its sort of a row's entries
+    // needs more terms to pay for rows of over 1024 (2000 groups of 8 882 and
+    // 1118, of 30 2744 and 2132).
+    const bool few_rows = n_qubits <= 11 && T >= 1024 && (G <= 1024 || T >= 24 * G);
+    const bool wide = n_qubits <= kMaxDense && G <= kMaxGroups && !few_rows;
     const int64_t cells = wide ? std::max<int64_t>(dim >> 6, 1) : 0;
     OpLayout L{};
     size_t off = 0;
@@ -771,9 +780,10 @@ try {
         VQE_HIP(ctx, hipStreamSynchronize(s));
     const unsigned rows64 = (unsigned)((dim + 63) / 64);
     const int fd = force_diag ? 1 : 0;
-    // waves per 64 rows: enough to fill the CUs, at least a few groups each (16
-    // against 8 at 14 qubits: 0.99 against 1.07 ms for an admitted run)
-    const int waves = G < 8 ? 1 : G < 64 ? 4 : 16;
+    // waves per 64 rows: one for each group up to 16 (16 against 8 at 14 qubits: 0.99
+    // against 1.07 ms for an admitted run; 4 against 16 for 30 groups of 200 terms at
+    // 12 qubits: 616 against 298 us)
+    const int waves = G < 2 ? 1 : G < 4 ? 2 : G < 8 ? 4 : G < 16 ? 8 : 16;
 
     if (!fill) {
         int64_t *h = ctx->host_scalars;

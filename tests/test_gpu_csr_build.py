@@ -82,11 +82,12 @@ def test_csr_build_shift_keeps_the_diagonal(ctx, n, identity):
     np.testing.assert_array_equal(d.val.cpu().numpy(), want.astype(np.complex64))
 
 
-@pytest.mark.parametrize("n,T,masks", [(9, 511, 200), (9, 512, 200), (12, 30000, 4096), (16, 20000, 1900), (23, 600, 2)])
+@pytest.mark.parametrize("n,T,masks", [(9, 511, 200), (9, 512, 200), (11, 1023, 60), (11, 1024, 60),
+                                       (11, 40000, 1700), (12, 30000, 4096), (16, 20000, 1900), (23, 600, 2)])
 def test_csr_build_term_order(ctx, n, T, masks):
     """Terms given in any order compile as the same terms grouped by flip mask
     beforehand (each group's in the given order), on both sides of the sizes where
-    the grouping changes."""
+    the grouping and the kernels change."""
     print(f"csr build order n={n} T={T} masks={masks}", flush=True)
     rng = np.random.default_rng(n)
     x = rng.choice(rng.choice(1 << n, size=masks, replace=False).astype(np.uint64), size=T)
