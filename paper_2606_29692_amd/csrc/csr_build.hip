@@ -49,20 +49,19 @@ constexpr int kInline = 1536;      // operator bytes passed as a kernel argument
 // smaller x >> 6 for every value of x >> 6 [cells + 1], the terms' z and their
 // folded coefficients (real parts only when every term is real).
 struct OpLayout {
-    uint32_t gs, cls, tz, tc;
+    uint64_t gs, cls, tz, tc;
     int32_t G;
 };
 struct OpInline {
     alignas(16) unsigned char b[kInline];
 };
-template <bool REAL> struct OpView {
-    const uint32_t *gx, *cls, *tz;
-    const int32_t *gs;
+template <bool REAL, bool INL = false> struct OpView {
+    const uint32_t *gx, *gs, *cls, *tz;
     const double *tc;
     __device__ __forceinline__ OpView(const unsigned char *b, const OpLayout &L)
     {
         gx = reinterpret_cast<const uint32_t *>(b);
-        gs = reinterpret_cast<const int32_t *>(b + L.gs);
+        gs = reinterpret_cast<const uint32_t *>(b + L.gs);
         cls = reinterpret_cast<const uint32_t *>(b + L.cls);
         tz = reinterpret_cast<const uint32_t *>(b + L.tz);
         tc = reinterpret_cast<const double *>(b + L.tc);
@@ -76,21 +75,32 @@ __device__ __forceinline__ double parity_sign(uint32_t v)
 }
 
 // Entry of column col contributed by group g, summed in ascending term order
-// (+-1 * c is exact, so each FMA is one addition).
-template <bool REAL>
-__device__ __forceinline__ double2 group_entry(const OpView<REAL> &op, int g, uint32_t col)
+// (+-1 * c is exact, so each FMA is one addition).  The kernel argument's terms
+// are indexed (a moving pointer into it would have it copied to scratch memory);
+// others, of which there may be more than 32-bit offsets reach, are walked by
+// pointer (16 qubits: 608 us, with 64-bit indexes 748).
+template <bool REAL, bool INL>
+__device__ __forceinline__ double2 group_entry(const OpView<REAL, INL> &op, int g, uint32_t col)
 {
     double re = 0.0, im = 0.0;
-    const int i1 = op.gs[g + 1];
+    const uint32_t i0 = op.gs[g], i1 = op.gs[g + 1];
+    auto add = [&](uint32_t z, const double *c) {
+        const double s = parity_sign(z & col);
+        re = fma(s, c[0], re);
+        if constexpr (!REAL)
+            im = fma(s, c[1], im);
+    };
+    constexpr int W = REAL ? 1 : 2;
+    if constexpr (INL) {
 #pragma unroll 4
-    for (int i = op.gs[g]; i < i1; i++) {
-        const double s = parity_sign(op.tz[i] & col);
-        if constexpr (REAL) {
-            re = fma(s, op.tc[i], re);
-        } else {
-            re = fma(s, op.tc[2 * i], re);
-            im = fma(s, op.tc[2 * i + 1], im);
-        }
+        for (int i = (int)i0; i < (int)i1; i++)
+            add(op.tz[i], &op.tc[W * i]);
+    } else {
+        const uint32_t *z = op.tz + i0;
+        const double *c = op.tc + (size_t)i0 * W;
+#pragma unroll 4
+        for (uint32_t i = i0; i < i1; i++, z++, c += W)
+            add(*z, c);
     }
     return make_double2(re, im);
 }
@@ -120,7 +130,7 @@ k_row_count(int64_t dim, OpInline inl, const unsigned char *__restrict__ mem, Op
             int force_diag, int32_t *__restrict__ counts, int32_t *__restrict__ onecol)
 {
     __shared__ int32_t s_cnt[16][64], s_col[16][64];
-    const OpView<REAL> op(INL ? inl.b : mem, L);
+    const OpView<REAL, INL> op(INL ? inl.b : mem, L);
     const int lane = threadIdx.x & 63, waves = blockDim.x >> 6;
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t r = (int64_t)blockIdx.x * 64 + lane;
@@ -158,7 +168,7 @@ k_row_fill(int64_t dim, OpInline inl, const unsigned char *__restrict__ mem, OpL
     extern __shared__ uint64_t bal[];                       // [G]
     uint16_t *order = reinterpret_cast<uint16_t *>(bal + L.G);   // [G]
     __shared__ int32_t s_cnt[2][16][64];
-    const OpView<REAL> op(INL ? inl.b : mem, L);
+    const OpView<REAL, INL> op(INL ? inl.b : mem, L);
     const int lane = threadIdx.x & 63, waves = blockDim.x >> 6;
     const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t r = (int64_t)blockIdx.x * 64 + lane;
@@ -689,12 +699,10 @@ try {
     const size_t o_gs = take((size_t)(G + 1) * 4), o_cls = take((size_t)(cells + 1) * 4);
     const size_t o_tz = take((size_t)T * 4), o_tc = take((size_t)T * (real ? 8 : 16));
     const size_t op_bytes = off;
-    if (op_bytes > 0x7fffffff)
-        return vqe_fail(ctx, VQE_ESIZE, "csr_build_from_pauli: too many terms");
-    L.gs = (uint32_t)o_gs;
-    L.cls = (uint32_t)o_cls;
-    L.tz = (uint32_t)o_tz;
-    L.tc = (uint32_t)o_tc;
+    L.gs = o_gs;
+    L.cls = o_cls;
+    L.tz = o_tz;
+    L.tc = o_tc;
     L.G = (int32_t)G;
     const bool inl = wide && op_bytes <= (size_t)kInline;
     // A small operator travels as a kernel argument, a larger one through the
@@ -721,7 +729,7 @@ try {
         b = blob.data();
     }
     uint32_t *h_gx = (uint32_t *)b, *h_cls = (uint32_t *)(b + o_cls), *h_tz = (uint32_t *)(b + o_tz);
-    int32_t *h_gs = (int32_t *)(b + o_gs);
+    uint32_t *h_gs = (uint32_t *)(b + o_gs);
     double *h_tc = (double *)(b + o_tc);
     int64_t g = 0, cell = 0;
     for (int64_t i = 0; i < T; i++) {
@@ -731,7 +739,7 @@ try {
             for (; cells && cell <= (int64_t)(x >> 6); cell++)
                 h_cls[cell] = (uint32_t)g;
             h_gx[g] = x;
-            h_gs[g++] = (int32_t)i;
+            h_gs[g++] = (uint32_t)i;
         }
         // i^{|x & z|} folded into the coefficient (exact)
         double re = 0.0, im = 0.0;
@@ -753,7 +761,7 @@ try {
             h_tc[2 * i + 1] = im;
         }
     }
-    h_gs[G] = (int32_t)T;
+    h_gs[G] = (uint32_t)T;
     for (; cells && cell <= cells; cell++)
         h_cls[cell] = (uint32_t)G;
 

@@ -126,3 +126,29 @@ def test_csr_build_of_many_terms_costs_no_more_out_of_order(ctx):
     mixed, grouped = best(x, z, c), best(x[at], z[at], c[at])
     print(f"csr build of {T} terms: out of order {mixed * 1e3:.2f} ms, grouped {grouped * 1e3:.2f} ms", flush=True)
     assert mixed <= 2 * grouped
+
+
+def test_csr_build_operator_past_2_gib(ctx):
+    """108 million complex terms (20 bytes each on the device) compile: some entries
+    against their ordered sums, bit for bit."""
+    n, G, per = 12, 2048, 52800
+    T = G * per
+    rng = np.random.default_rng(2)
+    xs = np.sort(rng.choice(1 << n, size=G, replace=False).astype(np.uint64))
+    x = np.repeat(xs, per)
+    z = np.resize(rng.integers(0, 1 << n, 999983).astype(np.uint64), T)
+    c = np.resize(rng.standard_normal(1000003) + 1j * rng.standard_normal(1000003), T)
+    print(f"csr build T={T}", flush=True)
+    d = B.csr_build_from_pauli(ctx, n, x, z, c, drop_tol=0.0)
+    torch.cuda.synchronize()
+    assert d.nnz == G << n and not d.real
+    for g in (0, 1, 1000, G - 1):
+        zg, cg = z[g * per:(g + 1) * per], c[g * per:(g + 1) * per]
+        k = np.bitwise_count(xs[g] & zg) % 4
+        cg = np.select([k == 0, k == 1, k == 2], [cg, -cg.imag + 1j * cg.real, -cg], cg.imag - 1j * cg.real)
+        for r in (0, 777, (1 << n) - 1):
+            col = r ^ int(xs[g])
+            v = np.where(np.bitwise_count(zg & np.uint64(col)) % 2 == 1, -cg, cg)
+            lo, hi = (int(i) for i in d.rowptr[r:r + 2].cpu())
+            cols, vals = d.col[lo:hi].cpu().numpy(), d.val[lo:hi].cpu().numpy()
+            assert vals[np.searchsorted(cols, col)] == np.cumsum(v.real)[-1] + 1j * np.cumsum(v.imag)[-1]
