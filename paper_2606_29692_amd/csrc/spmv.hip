@@ -4358,11 +4358,15 @@ extern "C" int32_t vqe_default_schedule(const vqe_csr *H)
     if (!H || H->dim <= 0)
         return 32;
     const double avg = (double)H->nnz / (double)H->dim;
-    // long rows: sixteen lanes of four entries (two passes and more of a row,
-    // few idle lanes in the last): 14 and 16 qubits, FP64, 22.8 and 140 us
-    // against 30.2 and 186 us with 64 lanes
+    // Long rows: sixteen lanes of four entries (two passes and more of a row, few
+    // idle lanes in the last) where their blocks of 32 rows give every CU two,
+    // from 2^14 rows on (14 and 16 qubits of molecules, FP64, 22.8 and 140 us
+    // against 30.2 and 186 with 64 lanes), or one with rows of a few passes (13
+    // qubits, 192 entries a row 13 against 17 us, 256 level, 512 35 against 27).
+    // Fewer rows leave CUs idle and each lane a long chain: 64 lanes (FP64, 10
+    // qubits of 512 entries a row 9 against 19 us, 12 of 2048 44 against 80).
     if (avg >= 96.0)
-        return 16 | VQE_SPMV_VEC4;
+        return H->dim >= 16384 || (H->dim >= 8192 && avg < 256.0) ? 16 | VQE_SPMV_VEC4 : 64 | VQE_SPMV_VEC4;
     if (avg >= 40.0)
         return 32;
     if (avg >= 12.0)
