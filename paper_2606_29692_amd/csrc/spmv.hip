@@ -190,9 +190,13 @@ k_spmv_energy(SpmvState single, const SpmvState *__restrict__ states,
 
 // A small single state in one workgroup, product, block sums and energy (the
 // same sums as k_spmv_energy and k_energy_finalize): up to SPMV_SMALL_DIM rows a
-// call is two launches' cost on the host rather than work (9.6 us a call, one
-// launch 6.3 us at 4 and 6 qubits, 7.6 us at 8).
+// call is two launches' cost on the host rather than work, as long as one
+// workgroup has few entries to read (a call among others 8.4 us, one launch 5.0
+// at 4 to 7 qubits of up to 16 entries a row, 5.7 at 6 of 64, 7.8 at 8 of 16;
+// at 7 of 64, 8192 entries, level and alone 19.4 against 18.2, at 8 of 64
+// 13.4 against 8.4).
 #define SPMV_SMALL_DIM 256
+#define SPMV_SMALL_NNZ 5120
 template <int DT, int L>
 __global__ void __launch_bounds__(1024)
 k_spmv_energy_small(SpmvState st)
@@ -4410,7 +4414,8 @@ int vqe_spmv_energy_core(vqe_ctx *ctx, const vqe_csr *H, const void *psi, void *
     st.nblocks = (int32_t)nblk;
     st.lanes = lanes;
     st.nnz = H->nnz;
-    if (dim <= SPMV_SMALL_DIM && (lanes == 8 || lanes == 16 || lanes == 32 || lanes == 64)) {
+    if (dim <= SPMV_SMALL_DIM && H->nnz <= SPMV_SMALL_NNZ &&
+        (lanes == 8 || lanes == 16 || lanes == 32 || lanes == 64)) {
         auto pick = [&](auto k8, auto k16, auto k32, auto k64) {
             return lanes == 8 ? k8 : lanes == 16 ? k16 : lanes == 32 ? k32 : k64;
         };

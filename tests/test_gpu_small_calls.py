@@ -107,3 +107,22 @@ def test_single_calls_and_plan(n, dtype):
             plan.close()
         assert torch.equal(*results)
         ctx.close()
+
+
+@pytest.mark.parametrize("masks", [20, 21, 64])
+def test_energy_of_few_rows_and_more_entries(masks):
+    """256 rows on both sides of the entries that one workgroup takes."""
+    print(f"small energy {masks} entries a row", flush=True)
+    ctx = P.Context(0)
+    rng = np.random.default_rng(masks)
+    x = rng.choice(256, size=masks, replace=False).astype(np.uint64)
+    H = B.csr_build_from_pauli(ctx, 8, x, rng.integers(0, 256, masks).astype(np.uint64), rng.standard_normal(masks) + 0j)
+    assert H.nnz == masks * 256
+    z = rng.standard_normal(256) + 1j * rng.standard_normal(256)
+    psi = torch.from_numpy(z).cuda()
+    sigma = torch.empty_like(psi)
+    e = B.energy(ctx, H, psi, sigma).cpu().numpy()
+    sg = _apply(_dense(H), z)
+    np.testing.assert_allclose(sigma.cpu().numpy(), sg, rtol=0, atol=1e-13 * masks * np.abs(sg).max())
+    assert abs(e[0] - np.vdot(z, sg).real / np.vdot(z, z).real) <= 1e-11
+    ctx.close()
