@@ -716,6 +716,9 @@ int enqueue_rest(vqe_batch *p, uint32_t flags, hipEvent_t *ev, const double *the
         launch_ls_dot(p->dtype, p->d_ls, p->d_ls_tasks, p->n_ls_tasks, s);
         launch_ls_solve(p->d_ls, (unsigned)p->B, s);
     }
+    // small states in one launch where that takes the place of several (the
+    // norm, or a copy of the angles)
+    const bool small = p->small_taylor && ((flags & VQE_STEP_RENORM) || theta_row);
     if (!(flags & VQE_STEP_NO_UPDATE)) {
         if (fused_fin)
             launch_taylor_mf_fin(p->dtype, p->d_tay, p->d_tay_tasks, p->n_tay_tasks, p->d_spmv,
@@ -723,7 +726,7 @@ int enqueue_rest(vqe_batch *p, uint32_t flags, hipEvent_t *ev, const double *the
                                  p->rel_tie, theta_row, s);
         else if (p->mf)
             launch_taylor_mf(p->dtype, p->d_tay, p->d_tay_tasks, p->n_tay_tasks, theta_row, s);
-        else if (p->small_taylor)
+        else if (small)
             launch_taylor_small(p->dtype, p->d_tay, (unsigned)p->B, p->compact_taylor,
                                 (flags & VQE_STEP_RENORM) != 0, theta_row, s);
         else if (p->compact_taylor)
@@ -732,7 +735,7 @@ int enqueue_rest(vqe_batch *p, uint32_t flags, hipEvent_t *ev, const double *the
             launch_taylor_pair(p->dtype, p->d_tay, p->d_tay_tasks, p->n_tay_tasks, s);
     }
     rc = rc ? rc : mark(5);
-    if (!(flags & VQE_STEP_NO_UPDATE) && (flags & VQE_STEP_RENORM) && !p->small_taylor) {
+    if (!(flags & VQE_STEP_NO_UPDATE) && (flags & VQE_STEP_RENORM) && !small) {
         if (p->mf)
             launch_norm_mf(p->dtype, p->d_tay, p->d_norm_tasks, p->n_norm_tasks, s);
         else
@@ -1696,8 +1699,9 @@ extern "C" int vqe_batch_run(vqe_batch *p, uint32_t flags, const double *theta_r
     if (n_steps == 0)
         return VQE_OK;
     const uint32_t sflags = flags & ~(uint32_t)VQE_STEP_GRAPH;
-    // each step with its row of angles: the matrix-free update reads the row
-    // itself; otherwise the row is first copied into the plan's angle buffer;
+    // each step with its row of angles: the matrix-free update and that of small
+    // CSR-pool states read the row themselves; otherwise the row is first copied
+    // into the plan's angle buffer;
     // with a line search each step chooses its own angles
     auto enqueue = [&]() -> int {
         for (int32_t i = 0; i < n_steps; i++) {

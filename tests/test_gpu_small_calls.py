@@ -109,6 +109,42 @@ def test_single_calls_and_plan(n, dtype):
         ctx.close()
 
 
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+@pytest.mark.parametrize("n", [4, 9, 11, 12])
+def test_updates_without_a_norm(n, dtype):
+    """An update that is neither normalised nor measured takes the wider kernel:
+    the same bits as one that is measured, alone and in a plan."""
+    print(f"small updates n={n} {dtype}", flush=True)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        ctx = P.Context(0, stream)
+        ham, packs = _packs(n)
+        H, pool = B.csr_from_pack(ctx, ham, dtype), B.pool_from_packs(ctx, packs, dtype)
+        rng = np.random.default_rng(n)
+        z = rng.standard_normal(1 << n) + 1j * rng.standard_normal(1 << n)
+        start = torch.from_numpy(z).cuda().to(torch.complex128 if dtype == "c128" else torch.complex64)
+        plain, measured = start.clone(), start.clone()
+        B.taylor5_apply(ctx, pool.ops[1], 0.07, plain, renormalize=False)
+        B.taylor5_apply(ctx, pool.ops[1], 0.07, measured, renormalize=False,
+                        norm2_out=torch.zeros(1, dtype=torch.float64, device="cuda"))
+        assert torch.equal(plain, measured)
+        rows = torch.full((1, 1), 0.07, dtype=torch.float64, device="cuda")
+        for run in (False, True):
+            psi = start.clone()
+            plan = B.BatchPlan(ctx, [(H, pool, psi)])
+            plan.theta.fill_(0.07)
+            plan.k.fill_(1)
+            if run:
+                plan.theta.zero_()
+                plan.run(rows, renorm=False, forced=True)
+            else:
+                plan.step(renorm=False, forced=True)
+            stream.synchronize()
+            assert torch.equal(psi, plain) and float(plan.theta[0]) == 0.07
+            plan.close()
+        ctx.close()
+
+
 @pytest.mark.parametrize("masks", [20, 21, 64])
 def test_energy_of_few_rows_and_more_entries(masks):
     """256 rows on both sides of the entries that one workgroup takes."""
