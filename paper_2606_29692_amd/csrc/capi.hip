@@ -906,11 +906,15 @@ extern "C" int vqe_batch_create(vqe_ctx *ctx, int32_t B, const vqe_batch_item *i
         load[x] += (double)items[s].H->nnz * 12.0 + (double)items[s].H->dim * 20.0;
     }
     // A state on one XCD keeps its vectors in one L2, but few states leave XCDs
-    // idle.  When the fullest has over 1.25 times its share and a state is of 2^14
-    // rows or more, every state's tasks go round all XCDs: a step of 2 states of
-    // 18 qubits 1276 -> 540 us, of 2 of 16 qubits 219 -> 179, of 1 of 14 qubits
-    // 43 -> 35; of smaller states it would lose (3 of 8 qubits 15.5 -> 17.0, 5 of
-    // 10 qubits 17.1 -> 18.8).
+    // idle.  When the fullest has well over its share and a state is of 2^14 rows
+    // or more, every state's tasks go round all XCDs.  A step on one XCD a state
+    // against this: 1 state of 14 qubits 88 and 41 us, 5 (1.6 times the share) 54
+    // and 47, 9 (1.8) 62 and 57, 11 (1.45) 66.5 and 67.2, 19 (1.26) 82 and 89; 2 of
+    // 16 qubits 225 and 83, 10 (1.6) 291 and 283, 11 (1.45) 302 and 321, 17 (1.4) 431
+    // and 470: from 1.5 on.  From 2^18 rows on already from 1.25: 2 of 18 qubits 959
+    // and 317, 6 (1.33) 1000 and 840, 18 (1.33) 2920 and 2380; 6 of 20 qubits 6590
+    // and 5270.  Smaller states would lose (3 of 8 qubits 15.5 and 17.0, 5 of 10
+    // qubits 17.1 and 18.8).
     const double share = std::accumulate(load.begin(), load.end(), 0.0) / kXcd;
     const int64_t top_dim = [&] {
         int64_t d = 0;
@@ -918,7 +922,8 @@ extern "C" int vqe_batch_create(vqe_ctx *ctx, int32_t B, const vqe_batch_item *i
             d = std::max<int64_t>(d, items[s].H->dim);
         return d;
     }();
-    p->spread = top_dim >= 16384 && *std::max_element(load.begin(), load.end()) > 1.25 * share;
+    const double full = *std::max_element(load.begin(), load.end()) / share;
+    p->spread = top_dim >= 16384 && full > (top_dim >= ((int64_t)1 << 18) ? 1.25 : 1.5);
     p->xcd = xcd_of;
 
     Arena A;
