@@ -666,7 +666,16 @@ class BatchPlan:
         for r, (_, _, psi) in zip(refs, self.states):
             if r.dtype != psi.dtype or r.numel() != psi.numel() or not r.is_contiguous():
                 raise ValueError("reoptimize: each reference must match its slot's state")
-        ptrs = (C.c_void_p * self.B)(*[r.data_ptr() for r in refs])
+        # kernels read the references: one that is elsewhere is first taken to the
+        # states' device, and its copy lives until the stream is done with it
+        at = []
+        for r, (_, _, psi) in zip(refs, self.states):
+            if r.device != psi.device:
+                r = r.to(psi.device)
+                self.ctx.stream.wait_stream(torch.cuda.current_stream(psi.device))
+                r.record_stream(self.ctx.stream)
+            at.append(r)
+        ptrs = (C.c_void_p * self.B)(*[r.data_ptr() for r in at])
         self.ctx.check(lib().vqe_batch_reoptimize(
             self.handle, ks.data_ptr(), thetas.data_ptr(), int(ks.shape[1]), int(n), ptrs,
             int(sweeps), float(theta_max), energies.data_ptr() if energies is not None else None),

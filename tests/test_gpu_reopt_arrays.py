@@ -49,3 +49,28 @@ def test_reoptimize_calls_in_a_row(dtype, states, n):
             alone.close()
         plan.close()
         ctx.close()
+
+
+def test_reoptimize_from_references_on_the_host():
+    """References in host memory, pageable and pinned, give what device ones give."""
+    n = 8
+    print("reopt host references", flush=True)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        ctx = P.Context(0, stream)
+        pools = PB.PoolCache(ctx, matrix_free=True)
+        ds = [PB.device_system(ctx, vs.make_system(vs.SystemSpec(n, vs.ELECTRONS[n], "jw", False, 9 + s)),
+                               "c64", pools) for s in range(2)]
+        refs = [d.psi.clone() for d in ds]
+        host = [refs[0].cpu(), refs[1].cpu().pin_memory()]
+        ks = torch.tensor([[0, 3, 5], [7, 2, 1]], dtype=torch.int32, device="cuda")
+        plan, out = PB.make_batch(ctx, ds), []
+        for ref in (refs, host, [refs[0], host[1]]):
+            th = torch.full((2, 3), 0.1, dtype=torch.float64, device="cuda")
+            plan.reoptimize(ks, th, 3, ref, 1, 1.0)
+            stream.synchronize()
+            out.append([th] + [d.psi.clone() for d in ds])
+        for other in out[1:]:
+            assert all(torch.equal(a, b) for a, b in zip(out[0], other))
+        plan.close()
+        ctx.close()
