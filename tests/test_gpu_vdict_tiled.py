@@ -121,3 +121,56 @@ def test_rebind(ctx, names):  # noqa: F811
             ctx.stream.synchronize()
             layout.close()
         plan.close()
+
+
+@pytest.mark.parametrize("call", ["run", "linesearch", "reoptimise"])
+def test_plan_calls_after_a_rebind(ctx, call):  # noqa: F811
+    """Replayed steps, line search and re-optimisation on a column-tiled dictionary:
+    a slot rebound to another operator and back gives the bits of a plan made for it,
+    and the energies of the layout without a dictionary (FP32 results of products
+    summed in another order: 2^-20 of the operator's bound)."""
+    with torch.cuda.stream(ctx.stream):
+        (n, A, pool), (_, H, _) = [_operator(ctx, k) for k in ("two_tiles", "complex")]
+        start = _state(n, "complex", 11)
+        rows = torch.tensor([[0.1], [-0.2]], dtype=torch.float64, device="cuda")
+        ks = torch.tensor([[0, 2, 1]], dtype=torch.int32, device="cuda")
+
+        def go(plan, psi):
+            th = torch.full((1, 3), 0.05, dtype=torch.float64, device="cuda")
+            psi.copy_(start)
+            if call == "run":
+                plan.run(rows)
+            elif call == "linesearch":
+                plan.set_line_search(0.5)
+                plan.run(None, line_search_steps=2)
+            else:
+                plan.reoptimize(ks, th, 3, [start], 1, 0.5)
+            plan.step(update=False, graph=True)
+            ctx.stream.synchronize()
+            return psi.clone(), th, plan.theta.clone(), plan.k.clone(), plan.energies.clone()
+
+        def alone(op, sched):
+            psi = start.clone()
+            plan = B.BatchPlan(ctx, [(op, pool, psi)], schedules=[sched])
+            out = go(plan, psi)
+            plan.close()
+            return out
+
+        psi = start.clone()
+        plan = B.BatchPlan(ctx, [(A, pool, psi)], schedules=[3 | VD])
+        built = B.Layout(ctx, A, 3 | VD)
+        for op, layout in ((A, None), (H, None), (A, built), (H, None), (A, None)):
+            print(f"vdict tiled {call} nnz={op.nnz} layout={layout is not None}", flush=True)
+            plan.rebind(0, op, pool, psi, layout=layout)
+            got = go(plan, psi)
+            want = alone(op, 3 | VD)
+            assert all(torch.equal(torch.view_as_real(a) if a.is_complex() else a,
+                                   torch.view_as_real(b) if b.is_complex() else b) for a, b in zip(got, want))
+            plain = alone(op, 2 | B.VQE_SPMV_LDS | B.VQE_SPMV_SLICED)
+            bound = float(op.val[:op.nnz].abs().max()) * op.nnz / op.dim
+            assert abs(float(got[4][0] - plain[4][0])) <= 2.0 ** -20 * bound
+            again = go(plan, psi)
+            assert all(torch.equal(torch.view_as_real(a) if a.is_complex() else a,
+                                   torch.view_as_real(b) if b.is_complex() else b) for a, b in zip(got, again))
+        plan.close()
+        built.close()
