@@ -33,7 +33,8 @@
  *     crosses the ABI.  vqe_last_error() gives a message for the last failure.
  *   - A context is not thread-safe: use one per host thread (or stream).
  *   - Results do not depend on how many states share a launch: the order of
- *     every floating-point sum is fixed by the operator's size alone.
+ *     every floating-point sum is fixed by the operator and the schedule (with
+ *     VQE_SPMV_VDICT by the operator's values too, else by its pattern).
  */
 #ifndef ADAPTVQE_H
 #define ADAPTVQE_H

@@ -33,51 +33,49 @@ k_pool_grad(const vqe_csr *__restrict__ ops, const void *__restrict__ psi,
     if (op.flags & VQE_PAIRING) {
         // pair {r, c} with A[r,c] = a, A[c,r] = b, handled by its lower row:
         // conj(sigma_r) a psi_c + conj(sigma_c) b psi_r
-        {
-            int k0[GRAD_ROWS], c[GRAD_ROWS], kb[GRAD_ROWS];
-            bool on[GRAD_ROWS];
+        int k0[GRAD_ROWS], c[GRAD_ROWS], kb[GRAD_ROWS];
+        bool on[GRAD_ROWS];
 #pragma unroll
-            for (int u = 0; u < GRAD_ROWS; u++) {
-                const int64_t r = r0 + (int64_t)u * nt;
-                on[u] = false;
-                k0[u] = 0;
-                if (r < dim) {
-                    k0[u] = rowptr[r];
-                    on[u] = rowptr[r + 1] != k0[u];
-                }
+        for (int u = 0; u < GRAD_ROWS; u++) {
+            const int64_t r = r0 + (int64_t)u * nt;
+            on[u] = false;
+            k0[u] = 0;
+            if (r < dim) {
+                k0[u] = rowptr[r];
+                on[u] = rowptr[r + 1] != k0[u];
             }
-#pragma unroll
-            for (int u = 0; u < GRAD_ROWS; u++)
-                c[u] = on[u] ? col[k0[u]] : 0;
-#pragma unroll
-            for (int u = 0; u < GRAD_ROWS; u++) {
-                on[u] = on[u] && c[u] >= r0 + (int64_t)u * nt;
-                kb[u] = on[u] ? rowptr[c[u]] : 0;
-            }
-            double2 a[GRAD_ROWS], b[GRAD_ROWS], pr[GRAD_ROWS], pc[GRAD_ROWS], qr[GRAD_ROWS], qc[GRAD_ROWS];
-#pragma unroll
-            for (int u = 0; u < GRAD_ROWS; u++)
-                if (on[u]) {
-                    const int64_t r = r0 + (int64_t)u * nt;
-                    a[u] = Elem<DT>::ld(op.val, k0[u]);
-                    b[u] = c[u] == r ? make_double2(0.0, 0.0) : Elem<DT>::ld(op.val, kb[u]);
-                    pr[u] = Elem<DT>::ld(psi, r);
-                    pc[u] = Elem<DT>::ld(psi, c[u]);
-                    qr[u] = Elem<DT>::ld(sigma, r);
-                    qc[u] = Elem<DT>::ld(sigma, c[u]);
-                }
-#pragma unroll
-            for (int u = 0; u < GRAD_ROWS; u++)
-                if (on[u]) {
-                    const double sr_x = qr[u].x + shift * pr[u].x, sr_y = qr[u].y + shift * pr[u].y;
-                    const double sc_x = qc[u].x + shift * pc[u].x, sc_y = qc[u].y + shift * pc[u].y;
-                    const double wr = a[u].x * pc[u].x - a[u].y * pc[u].y;
-                    const double wi = a[u].x * pc[u].y + a[u].y * pc[u].x;
-                    const double ur = b[u].x * pr[u].x - b[u].y * pr[u].y;
-                    const double ui = b[u].x * pr[u].y + b[u].y * pr[u].x;
-                    acc += (sr_x * wr + sr_y * wi) + (sc_x * ur + sc_y * ui);
-                }
         }
+#pragma unroll
+        for (int u = 0; u < GRAD_ROWS; u++)
+            c[u] = on[u] ? col[k0[u]] : 0;
+#pragma unroll
+        for (int u = 0; u < GRAD_ROWS; u++) {
+            on[u] = on[u] && c[u] >= r0 + (int64_t)u * nt;
+            kb[u] = on[u] ? rowptr[c[u]] : 0;
+        }
+        double2 a[GRAD_ROWS], b[GRAD_ROWS], pr[GRAD_ROWS], pc[GRAD_ROWS], qr[GRAD_ROWS], qc[GRAD_ROWS];
+#pragma unroll
+        for (int u = 0; u < GRAD_ROWS; u++)
+            if (on[u]) {
+                const int64_t r = r0 + (int64_t)u * nt;
+                a[u] = Elem<DT>::ld(op.val, k0[u]);
+                b[u] = c[u] == r ? make_double2(0.0, 0.0) : Elem<DT>::ld(op.val, kb[u]);
+                pr[u] = Elem<DT>::ld(psi, r);
+                pc[u] = Elem<DT>::ld(psi, c[u]);
+                qr[u] = Elem<DT>::ld(sigma, r);
+                qc[u] = Elem<DT>::ld(sigma, c[u]);
+            }
+#pragma unroll
+        for (int u = 0; u < GRAD_ROWS; u++)
+            if (on[u]) {
+                const double sr_x = qr[u].x + shift * pr[u].x, sr_y = qr[u].y + shift * pr[u].y;
+                const double sc_x = qc[u].x + shift * pc[u].x, sc_y = qc[u].y + shift * pc[u].y;
+                const double wr = a[u].x * pc[u].x - a[u].y * pc[u].y;
+                const double wi = a[u].x * pc[u].y + a[u].y * pc[u].x;
+                const double ur = b[u].x * pr[u].x - b[u].y * pr[u].y;
+                const double ui = b[u].x * pr[u].y + b[u].y * pr[u].x;
+                acc += (sr_x * wr + sr_y * wi) + (sc_x * ur + sc_y * ui);
+            }
     } else {
         for (int64_t r = r0; r < dim && r < r0 + GRAD_CHUNK; r += nt) {
             const int k0 = rowptr[r], k1 = rowptr[r + 1];

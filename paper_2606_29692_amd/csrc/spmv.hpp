@@ -150,19 +150,13 @@ struct SpmvState {
 #define SPMV_VDT_MAX_DIM ((int64_t)1 << 20)
 #define SPMV_VDT_TILES 64
 #define SPMV_VDT_GROUP 4
-#ifndef SPMV_VDT_DEPTH
 #define SPMV_VDT_DEPTH 2
-#endif
-#ifndef SPMV_VDT_ODEPTH
 #define SPMV_VDT_ODEPTH 1
-#endif
 #define SPMV_VD_VALS 4
 // entries per group of an operator with more masks than the index form takes
 #define SPMV_VD_COLS(real) ((real) ? 4 : 2)
 #define SPMV_VD_GROUP 10
-#ifndef SPMV_VD_DEPTH
 #define SPMV_VD_DEPTH 3
-#endif
 // largest dimension whose column XOR row fits 16 bits
 #define SPMV_X16_MAX_DIM 65536
 // row length granule of the padded layout (real values, states that fit LDS)

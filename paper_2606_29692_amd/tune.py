@@ -7,13 +7,16 @@ values in the row-padded layout (PAD), for a real H the real values in
 that layout (REAL), and the sliced layout with one row per lane (SLICED,
 with 2, 4 or 8 entries per lane and load in place of the lanes, or 3 or 6
 with the flip masks' 10-bit indices in place of the columns, XIDX, and a
-dictionary of the values, VDICT; an operator with too many masks for it times
-as infinite).  It is picked
-per (register size, dtype, mapping, value form, device) by timing the batched
-H product phase of a real plan over the candidates, and cached.  The value
-form "complex" keeps the interleaved complex values of the CSR (candidates
-without REAL); "any" also admits REAL, which applies to Hamiltonians whose
-entries are all real.  The choice is a function of that key alone, so a state
+dictionary of the values, VDICT; an operator with too many masks for the index
+form alone times as infinite, one with the dictionary falls back to columns).
+It is picked per (register size, dtype, mapping, value form, device) by timing
+the batched H product phase of a real plan over the candidates, and cached.
+The value form "complex" is for complex states: candidates without REAL, which
+multiply in complex arithmetic (VDICT's dictionary holds real magnitudes, and
+what it keeps beside them are real parts for an operator flagged VQE_REAL, the
+complex values of any other; the other candidates stream the CSR's interleaved
+complex values).  "any" also admits REAL, which looks for a real state and
+applies to Hamiltonians whose entries are all real.  The choice is a function of that key alone, so a state
 gets the same schedule (and the same floating-point summation order) whether
 it runs alone or inside any batch.
 
@@ -143,7 +146,7 @@ def tune_schedule(ctx, systems, candidates=CANDIDATES) -> dict:
 def schedule_for(ctx, ds, systems=None, retune: bool = False, value_form: str = "any") -> int:
     """Tuned schedule for systems shaped like ``ds`` (tuning on ``systems`` or
     [ds] when no cached entry exists); value_form "complex" restricts the
-    candidates to schedules that stream the complex values."""
+    candidates to schedules without VQE_SPMV_REAL, for complex states."""
     key = _key(ctx, ds, value_form)
     if not retune:
         if key in _memo:
