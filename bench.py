@@ -914,7 +914,7 @@ def main():
                         f"orbitals, {vs.ELECTRONS[args.qubits]} electrons, {args.mapping.upper()}), "
                         f"H nnz {hnnz} each, pool {ds[0].pool.M} shared; one adaptive step per state per "
                         f"launch sequence (H SpMV + FP64 energy, {ds[0].pool.M}-generator gradient screen, "
-                        f"argmax, fused Taylor-O(5), FP64 renorm); {head['value_form']} values, "
+                        f"argmax, fused Taylor-O(5), FP64 renorm); values: {head['value_form']}; "
                         f"{form} states",
             "states": len(ds), "n_qubits": args.qubits, "n_electrons": vs.ELECTRONS[args.qubits],
             "mapping": args.mapping, "pool": ds[0].pool.M, "storage": args.dtype,

@@ -23,12 +23,12 @@
 // entry its place.
 //
 // Measured (one MI355X, both calls and their allocations): H at 16 qubits, FP64,
-// 18.2 M entries, 6.12 -> 0.63 ms, of which the sizing kernel is 0.11 ms and the
-// fill 0.41 ms (evaluating and storing overlap: 0.32 ms without either); the 92
-// generators of a 12-qubit pool 16.9 -> 3.2 ms.  Before, the terms were sorted
-// on the device by one launch per bitonic step, one wave took one row with its
-// groups over the lanes (a wave waits for its longest group) and the kept
-// entries were sorted in LDS.
+// 18.2 M entries, 6.12 -> 0.61 ms, of which the sizing kernel is 0.10 ms and the
+// fill 0.40 ms; the 92 generators of a 12-qubit pool 16.9 -> 3.2 ms.  Before, the
+// terms were sorted on the device by one launch per bitonic step, one wave took
+// one row with its groups over the lanes (a wave waits for its longest group) and
+// the kept entries were sorted in LDS; that form of the kernels is left where
+// few rows have many terms.
 //
 // This file is built with -ffp-contract=off.
 #include "common.hpp"
