@@ -174,18 +174,18 @@ k_taylor_small(TaylorState single, const TaylorState *__restrict__ states, bool 
                const double *__restrict__ theta_row)
 {
     const TaylorState *stp = BATCH ? states + blockIdx.x : &single;
-    if (BATCH && VQE_SKIP(*stp))
-        return;
     const int tid = threadIdx.x, n = (int)stp->dim;
-    void *psi = stp->psi;
-    const int32_t kk = stp->k ? *stp->k : 0;
     double theta = stp->theta_value;
     if (BATCH) {
         theta = theta_row ? theta_row[blockIdx.x] : *stp->theta;
         __syncthreads();      // (every thread has read the angle)
         if (theta_row && tid == 0)
-            *const_cast<double *>(stp->theta) = theta;
+            *const_cast<double *>(stp->theta) = theta;     // a skipped slot's too
+        if (VQE_SKIP(*stp))
+            return;
     }
+    void *psi = stp->psi;
+    const int32_t kk = stp->k ? *stp->k : 0;
     if (!stp->k || (kk >= 0 && kk < stp->M)) {
         if (BATCH && compact) {
             const PairTable *tb = stp->table;

@@ -145,6 +145,30 @@ def test_updates_without_a_norm(n, dtype):
         ctx.close()
 
 
+@pytest.mark.parametrize("n", [8, 12])
+def test_angle_rows_reach_skipped_slots(n):
+    """After a run every slot of a CSR-pool plan holds its last angle, a slot that is
+    switched off too, whether the update reads the rows itself or they are copied."""
+    print(f"angles of skipped slots n={n}", flush=True)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        ctx = P.Context(0, stream)
+        ham, packs = _packs(n)
+        H, pool = B.csr_from_pack(ctx, ham), B.pool_from_packs(ctx, packs)
+        states = [torch.full((1 << n,), 2.0 ** (-n / 2), dtype=torch.complex128, device="cuda") for _ in range(3)]
+        plan = B.BatchPlan(ctx, [(H, pool, p) for p in states], with_active=True)
+        plan.active[1] = 0
+        before = states[1].clone()
+        rows = torch.tensor([[0.1, 0.2, 0.3], [0.4, 0.5, 0.6]], dtype=torch.float64, device="cuda")
+        for graph in (False, True):
+            plan.theta.zero_()
+            plan.run(rows, graph=graph)
+            stream.synchronize()
+            assert torch.equal(plan.theta, rows[1]) and torch.equal(states[1], before)
+        plan.close()
+        ctx.close()
+
+
 @pytest.mark.parametrize("masks", [20, 21, 64])
 def test_energy_of_few_rows_and_more_entries(masks):
     """256 rows on both sides of the entries that one workgroup takes."""
